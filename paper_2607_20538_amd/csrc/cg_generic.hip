@@ -10,77 +10,12 @@
 // large-group bf16 block-uniform case.
 #include "cg_internal.h"
 #include "cg_device.h"
+#include "cg_general.h"
 #include "cg_zfp.h"
 
 namespace cg {
 
 namespace {
-
-constexpr int kThreads = 256;
-
-__device__ __forceinline__ size_t gauge_block(int l, int s, int h, int r, int H, int R) {
-  return ((size_t(l) * 2 + s) * H + h) * R + r;
-}
-
-__device__ __forceinline__ float load_x(const ViewDev& v, size_t off) {
-  return v.bf16 ? bf16_to_f32(((const uint16_t*)v.ptr)[off]) : ((const float*)v.ptr)[off];
-}
-
-// LDS row pitch of the token tiles (floats): a multiple of 4 so that rows stay 16-byte aligned
-// for vector reads, offset by 4 banks from row to row
-constexpr int kPad = 4;
-
-// zs[t][i] = sum_j G_{l,s,h,r}[i%g][j] xs[t][r*g + j] for t < ntok: one binary32 FMA chain per
-// element in increasing j.  With g a multiple of 4 each thread computes a 4-token x 4-channel
-// block, reading 4 consecutive j of 4 rows of G and of 4 token rows per step (16-byte loads).
-__device__ void gauge_tile(const float* xs, float* zs, int ntok, int d, int dp, const GaugeDev& G, int l, int s,
-                           int h) {
-  const int g = G.g;
-  if (g % 4) {
-    for (int idx = threadIdx.x; idx < ntok * d; idx += blockDim.x) {
-      const int t = idx / d, i = idx - t * d;
-      const int r = i / g, ii = i - r * g;
-      const float* Gr = G.f32 + gauge_block(l, s, h, r, G.H, G.R) * g * g + size_t(ii) * g;
-      const float* xr = xs + t * dp + r * g;
-      float acc = 0.0f;
-      for (int j = 0; j < g; ++j) acc = fmaf(Gr[j], xr[j], acc);
-      zs[t * dp + i] = acc;
-    }
-    return;
-  }
-  const int ntb = (ntok + 3) / 4, ncb = d / 4;
-  for (int idx = threadIdx.x; idx < ntb * ncb; idx += blockDim.x) {
-    const int tb = idx / ncb, cb = idx - tb * ncb;
-    const int t0 = 4 * tb, i0 = 4 * cb, r = i0 / g;
-    const float* Gb = G.f32 + gauge_block(l, s, h, r, G.H, G.R) * g * g + size_t(i0 - r * g) * g;
-    const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    float acc[4][4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int a = 0; a < 4; ++a) acc[t][a] = 0.0f;
-    for (int j = 0; j < g; j += 4) {
-      float4 gv[4], xv[4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) gv[a] = *reinterpret_cast<const float4*>(Gb + size_t(a) * g + j);
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        xv[t] = t0 + t < ntok ? *reinterpret_cast<const float4*>(xs + (t0 + t) * dp + r * g + j) : zero;
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          acc[t][a] = fmaf(gv[a].x, xv[t].x, acc[t][a]);
-          acc[t][a] = fmaf(gv[a].y, xv[t].y, acc[t][a]);
-          acc[t][a] = fmaf(gv[a].z, xv[t].z, acc[t][a]);
-          acc[t][a] = fmaf(gv[a].w, xv[t].w, acc[t][a]);
-        }
-    }
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-      if (t0 + t < ntok) *reinterpret_cast<float4*>(zs + (t0 + t) * dp + i0) = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
-  }
-}
 
 // xs[t][i] = sum_j G_{l,s,h,r}[j][i%g] zs[t][r*g + j] (inverse gauge, G^T), the same chains and
 // blocking (4 consecutive columns of G are one 16-byte read of row j).
@@ -132,107 +67,6 @@ __device__ void inverse_tile(const float* zs, float* xs, int ntok, int d, int dp
 #pragma unroll
     for (int t = 0; t < 4; ++t)
       if (t0 + t < ntok) *reinterpret_cast<float4*>(xs + (t0 + t) * dp + i0) = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
-  }
-}
-
-// Quantise n values (stride `stride` in LDS) as one block and write its packed stream and
-// side word.  n * bits is a multiple of 32.
-__device__ int quantize_block_to(const float* z, int stride, int n, int bits, uint32_t* dst, uint32_t* side_dst) {
-  float mn = z[0], mx = z[0];
-  for (int e = 1; e < n; ++e) {
-    mn = fminf(mn, z[e * stride]);
-    mx = fmaxf(mx, z[e * stride]);
-  }
-  Side sd = make_side(mn, mx, bits);
-  const float qmax = (float)((1 << bits) - 1);
-  uint64_t acc = 0;
-  int nbit = 0, wi = 0;
-  for (int e = 0; e < n; ++e) {
-    acc |= (uint64_t)quantize(z[e * stride], sd.mn, sd.inv, qmax) << nbit;
-    nbit += bits;
-    if (nbit >= 32) {
-      dst[wi++] = (uint32_t)acc;
-      acc >>= 32;
-      nbit -= 32;
-    }
-  }
-  *side_dst = sd.word;
-  return sd.flags;
-}
-
-// Block-uniform (or KIVI value) rows: tile rows t < ntok go to cache positions pos0 + t.
-__device__ int store_rows_blocks(const float* zs, int ntok, int d, int dp, int n, int bits, const CacheDev& k,
-                                 size_t slc, int pos0) {
-  int flags = 0;
-  const int nb = d / n, row_bytes = d * bits / 8, blk_bytes = n * bits / 8;
-  for (int w = threadIdx.x; w < ntok * nb; w += blockDim.x) {
-    const int t = w / nb, kb = w - t * nb;
-    const size_t row = slc * k.T_cap + pos0 + t;
-    uint32_t* dst = (uint32_t*)(k.codes + row * row_bytes + size_t(kb) * blk_bytes);
-    flags |= quantize_block_to(zs + t * dp + kb * n, 1, n, bits, dst, k.side + row * nb + kb);
-  }
-  return flags;
-}
-
-// Block-uniform token-channel tiles: tile rows [u*bt, u*bt + bt) form tile (pos0 / bt) + u; one
-// (tile, channel block) per thread takes the range of its bt x n values and packs every token's
-// n codes into that token's row.
-__device__ int store_tiles(const float* zs, int ntile, int bt, int d, int dp, int n, int bits, const CacheDev& k,
-                           size_t slc, int pos0) {
-  int flags = 0;
-  const int nb = d / n, row_bytes = d * bits / 8, blk_bytes = n * bits / 8;
-  for (int w = threadIdx.x; w < ntile * nb; w += blockDim.x) {
-    const int u = w / nb, kb = w - u * nb;
-    const float* zt = zs + (u * bt) * dp + kb * n;
-    float mn = zt[0], mx = zt[0];
-    for (int v = 0; v < bt; ++v)
-      for (int e = 0; e < n; ++e) {
-        mn = fminf(mn, zt[v * dp + e]);
-        mx = fmaxf(mx, zt[v * dp + e]);
-      }
-    const Side sd = make_side(mn, mx, bits);
-    const float qmax = (float)((1 << bits) - 1);
-    for (int v = 0; v < bt; ++v) {
-      const size_t row = slc * k.T_cap + pos0 + u * bt + v;
-      uint32_t* dst = (uint32_t*)(k.codes + row * row_bytes + size_t(kb) * blk_bytes);
-      uint64_t acc = 0;
-      int nbit = 0, wi = 0;
-      for (int e = 0; e < n; ++e) {
-        acc |= (uint64_t)quantize(zt[v * dp + e], sd.mn, sd.inv, qmax) << nbit;
-        nbit += bits;
-        if (nbit >= 32) {
-          dst[wi++] = (uint32_t)acc;
-          acc >>= 32;
-          nbit -= 32;
-        }
-      }
-    }
-    k.side[(slc * (k.T_cap / bt) + (pos0 / bt + u)) * nb + kb] = sd.word;
-    flags |= sd.flags;
-  }
-  return flags;
-}
-
-// KIVI key groups: tile rows [u*kg, u*kg + kg) form token group grp0 + u; one channel per
-// thread.
-__device__ int store_key_groups(const float* zs, int ngrp, int kg, int d, int dp, int bits, const CacheDev& k,
-                                size_t slc, int grp0) {
-  int flags = 0;
-  const int cb = kg * bits / 8;
-  for (int w = threadIdx.x; w < ngrp * d; w += blockDim.x) {
-    const int u = w / d, ch = w - u * d;
-    const size_t gi = slc * (k.T_cap / kg) + grp0 + u;
-    uint32_t* dst = (uint32_t*)(k.codes + (gi * d + ch) * cb);
-    flags |= quantize_block_to(zs + (u * kg) * dp + ch, dp, kg, bits, dst, k.side + gi * d + ch);
-  }
-  return flags;
-}
-
-__device__ void store_rows_pass(const float* zs, int ntok, int d, int dp, const CacheDev& k, size_t slc, int pos0) {
-  float* out = (float*)k.codes;
-  for (int idx = threadIdx.x; idx < ntok * d; idx += blockDim.x) {
-    const int t = idx / d, ch = idx - t * d;
-    out[(slc * k.T_cap + pos0 + t) * d + ch] = zs[t * dp + ch];
   }
 }
 
@@ -457,100 +291,9 @@ __global__ __launch_bounds__(kThreads) void dec_generic(int s, CacheDev k, int l
   }
 }
 
-// ------------------------------------------------------------------------------------------
-// rolling append: one workgroup per (layer, b, h)
-// ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void append_generic(int s, ViewDev Xn, int l0, const int* pos, GaugeDev G,
-                                                           CodecDev c, CacheDev k, int* err, PageDev pt) {
-  extern __shared__ float sm[];
-  const int d = Xn.d, dp = d + kPad;
-  const int sv = blockIdx.x;
-  const int h = sv % Xn.H, b = (sv / Xn.H) % Xn.B, lv = sv / (Xn.H * Xn.B);
-  const int l = lv + l0;
-  const size_t xbase = size_t(lv) * Xn.sl + size_t(b) * Xn.sb + size_t(h) * Xn.sh;
-  int p = pos[b];
-  int row = b;  // cache batch row (the page of a paged cache)
-  if (pt.pages) {
-    // the position's page; a position past the table or a page outside the pool is an error
-    const int lp = p >= 0 ? p / pt.page_size : -1;
-    row = lp >= 0 && lp < pt.max_pages ? pt.pages[size_t(b) * pt.max_pages + lp] : -1;
-    if (row < 0 || row >= k.B) {
-      if (threadIdx.x == 0 && err) atomicOr(err, CG_FLAG_POS_RANGE);
-      return;
-    }
-    p -= lp * pt.page_size;
-  }
-  const size_t slc = (size_t(l) * k.B + row) * k.H + h;
-  if (p < 0 || p >= k.T_cap) {
-    if (threadIdx.x == 0 && err) atomicOr(err, CG_FLAG_POS_RANGE);
-    return;
-  }
-  int flags = 0;
-  if (c.backend == CG_BACKEND_KIVI) {
-    const int ringsz = c.win + c.kg;
-    const uint16_t* src = (const uint16_t*)Xn.ptr + xbase;
-    for (int ch = threadIdx.x; ch < d; ch += blockDim.x) k.ring[(slc * ringsz + p % ringsz) * d + ch] = src[ch];
-    const int T = p + 1;
-    if (!(T - c.win >= c.kg && (T - c.win) % c.kg == 0)) return;
-    __syncthreads();
-    // flush the kg oldest window tokens [T - W - kg, T - W)
-    const int tb = T - c.win - c.kg;
-    float* xs = sm;
-    float* zs = sm + c.kg * dp;
-    for (int idx = threadIdx.x; idx < c.kg * d; idx += blockDim.x) {
-      const int t = idx / d, ch = idx - t * d;
-      xs[t * dp + ch] = bf16_to_f32(k.ring[(slc * ringsz + (tb + t) % ringsz) * d + ch]);
-    }
-    __syncthreads();
-    gauge_tile(xs, zs, c.kg, d, dp, G, l, s, h);
-    __syncthreads();
-    if (s == 0) flags |= store_key_groups(zs, 1, c.kg, d, dp, c.bits, k, slc, tb / c.kg);
-    else flags |= store_rows_blocks(zs, c.kg, d, dp, c.kvc, c.bits, k, slc, tb);
-  } else if (c.backend == CG_BACKEND_BLOCK_UNIFORM && c.bt > 1) {
-    // stage the token; its tile is quantised once the tile's last token is there
-    const uint16_t* src = (const uint16_t*)Xn.ptr + xbase;
-    for (int ch = threadIdx.x; ch < d; ch += blockDim.x) k.ring[(slc * c.bt + p % c.bt) * d + ch] = src[ch];
-    if ((p + 1) % c.bt == 0) {
-      __syncthreads();
-      const int tb = p + 1 - c.bt;
-      float* xs = sm;
-      float* zs = sm + c.bt * dp;
-      for (int idx = threadIdx.x; idx < c.bt * d; idx += blockDim.x) {
-        const int t = idx / d, ch = idx - t * d;
-        const float v = bf16_to_f32(k.ring[(slc * c.bt + (tb + t) % c.bt) * d + ch]);
-        if (!isfinite(v)) flags |= CG_FLAG_NONFINITE;
-        xs[t * dp + ch] = v;
-      }
-      __syncthreads();
-      gauge_tile(xs, zs, c.bt, d, dp, G, l, s, h);
-      __syncthreads();
-      flags |= store_tiles(zs, 1, c.bt, d, dp, c.n, c.bits, k, slc, tb);
-    }
-  } else {
-    float* xs = sm;
-    float* zs = sm + dp;
-    for (int ch = threadIdx.x; ch < d; ch += blockDim.x) {
-      const float v = load_x(Xn, xbase + ch);
-      if (!isfinite(v)) flags |= CG_FLAG_NONFINITE;
-      xs[ch] = v;
-    }
-    __syncthreads();
-    gauge_tile(xs, zs, 1, d, dp, G, l, s, h);
-    __syncthreads();
-    if (c.backend == CG_BACKEND_PASSTHROUGH) store_rows_pass(zs, 1, d, dp, k, slc, p);
-    else flags |= store_rows_blocks(zs, 1, d, dp, c.n, c.bits, k, slc, p);
-  }
-  if (flags && err) atomicOr(err, flags);
-}
-
 // KIVI tiles are exactly one key token group, so the quantised / window split (a multiple of
 // the group) never cuts a tile.
 int tile_tokens(const CodecDev& c) { return c.backend == CG_BACKEND_KIVI ? c.kg : 32; }
-
-hipError_t set_smem(const void* fn, size_t bytes) {
-  if (bytes <= 65536) return hipSuccess;
-  return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-}
 
 }  // namespace
 
@@ -575,17 +318,6 @@ hipError_t launch_decode_generic(int s, const CacheDev& k, int l0, const GaugeDe
   if (e != hipSuccess) return e;
   dim3 grid((Y.T + TT - 1) / TT, Y.L * Y.B * Y.H);
   hipLaunchKernelGGL(dec_generic, grid, dim3(kThreads), smem, st, s, k, l0, G, c, t0, len, pos, pos_add, Y, TT, err);
-  return hipGetLastError();
-}
-
-hipError_t launch_append(int s, const ViewDev& Xn, int l0, const int* pos, const GaugeDev& G, const CodecDev& c,
-                         const CacheDev& k, int* err, hipStream_t st, const PageDev& pt) {
-  const int rows = c.backend == CG_BACKEND_KIVI ? c.kg : c.bt;
-  const size_t smem = size_t(2) * rows * (Xn.d + kPad) * sizeof(float);
-  hipError_t e = set_smem((const void*)append_generic, smem);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(append_generic, dim3(Xn.L * Xn.B * Xn.H), dim3(kThreads), smem, st, s, Xn, l0, pos, G, c, k,
-                     err, pt);
   return hipGetLastError();
 }
 

@@ -638,8 +638,8 @@ int32_t kv_append_step(int32_t l0, int32_t l1, const cg_kv_view* k_new, const cg
   hipStream_t st = static_cast<hipStream_t>(stream);
   const GaugeDev G = gauge_dev(G_dev, shp);
   const CodecDev c = codec_dev(codec);
-  hipError_t e = launch_append(0, view_dev(k_new), l0, pos, G, c, cache_dev(kc), err_flag, st);
-  if (e == hipSuccess) e = launch_append(1, view_dev(v_new), l0, pos, G, c, cache_dev(vc), err_flag, st);
+  hipError_t e =
+      launch_append(view_dev(k_new), view_dev(v_new), l0, pos, G, c, cache_dev(kc), cache_dev(vc), err_flag, st);
   if (e == hipSuccess && k_hist)
     e = launch_decode(0, cache_dev(kc), l0, G, c, 0, 0, pos, 1, view_dev(k_hist), err_flag, st);
   if (e == hipSuccess && v_hist)
@@ -885,8 +885,8 @@ int32_t kv_append_paged(int32_t l0, int32_t l1, const cg_kv_view* k_new, const c
   pt.pages = pages->pages;
   pt.max_pages = pages->max_pages;
   pt.page_size = pages->page_size;
-  hipError_t e = launch_append(0, view_dev(k_new), l0, pos, G, c, cache_dev(kc), err_flag, st, pt);
-  if (e == hipSuccess) e = launch_append(1, view_dev(v_new), l0, pos, G, c, cache_dev(vc), err_flag, st, pt);
+  hipError_t e =
+      launch_append(view_dev(k_new), view_dev(v_new), l0, pos, G, c, cache_dev(kc), cache_dev(vc), err_flag, st, pt);
   return e == hipSuccess ? CG_OK : CG_ERR_DEVICE;
 }
 

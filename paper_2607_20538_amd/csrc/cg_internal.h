@@ -178,8 +178,10 @@ hipError_t launch_encode(int s, const ViewDev& X, int l0, const GaugeDev& G, con
 // the row); otherwise every row holds `len` tokens (KIVI window and tile staging split).
 hipError_t launch_decode(int s, const CacheDev& k, int l0, const GaugeDev& G, const CodecDev& c, int t0, int len,
                          const int* pos, int pos_add, const ViewDev& Y, int* err, hipStream_t st);
-// Rolling append of one token per (layer, b, h) at pos[b] (layer l of Xn is cache layer l + l0).
-hipError_t launch_append(int s, const ViewDev& Xn, int l0, const int* pos, const GaugeDev& G, const CodecDev& c,
-                         const CacheDev& k, int* err, hipStream_t st, const PageDev& pt = PageDev());
+// Rolling append of one key and one value token per (layer, b, h) at pos[b], in one launch (layer l of
+// the views is cache layer l + l0).
+hipError_t launch_append(const ViewDev& Kn, const ViewDev& Vn, int l0, const int* pos, const GaugeDev& G,
+                         const CodecDev& c, const CacheDev& kc, const CacheDev& vc, int* err, hipStream_t st,
+                         const PageDev& pt = PageDev());
 
 }  // namespace cg
