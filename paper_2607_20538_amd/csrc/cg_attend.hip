@@ -78,33 +78,6 @@ __device__ __forceinline__ bool step_slice(const AttendDev& a, int l, int b, int
   return true;
 }
 
-// zhat of channel ch at quantised cache position p of slice slc (section 4.3 decode).
-__device__ __forceinline__ float zhat_at(const CacheDev& k, const CodecDev& c, int s, size_t slc, int p, int ch,
-                                         int d) {
-  if (c.backend == CG_BACKEND_PASSTHROUGH) return ((const float*)k.codes)[(slc * k.T_cap + p) * d + ch];
-  const int bits = c.bits;
-  uint32_t q, sw;
-  if (c.backend == CG_BACKEND_BLOCK_UNIFORM || s == 1) {
-    // token rows: the d/n blocks of a row form one LSB-first stream
-    const int n = c.backend == CG_BACKEND_BLOCK_UNIFORM ? c.n : c.kvc;
-    const size_t row = slc * k.T_cap + p;
-    q = extract_code((const uint32_t*)(k.codes + row * (d * bits / 8)), ch, bits);
-    sw = k.side[(c.bt > 1 ? slc * (k.T_cap / c.bt) + p / c.bt : row) * (d / n) + ch / n];
-  } else {
-    // KIVI keys: one stream per (token group, channel)
-    const int kg = c.kg;
-    const size_t gi = slc * (k.T_cap / kg) + p / kg;
-    q = extract_code((const uint32_t*)(k.codes + (gi * d + ch) * (kg * bits / 8)), p % kg, bits);
-    sw = k.side[gi * d + ch];
-  }
-  return dequantize(q, f16_bits_to_f32(sw & 0xffffu), f16_bits_to_f32(sw >> 16));
-}
-
-__device__ __forceinline__ float raw_at(const CacheDev& k, const CodecDev& c, size_t slc, int p, int ch, int d) {
-  const int ringsz = c.backend == CG_BACKEND_KIVI ? c.win + c.kg : c.bt;
-  return bf16_to_f32(k.ring[(slc * ringsz + p % ringsz) * d + ch]);
-}
-
 // Channels ch0 .. ch0 + 7 (ch0 % 8 == 0) of cache position p: raw bf16 tokens (raw) or the
 // dequantised gauge-space values, with as few loads as the layout allows (one or two dwords of a
 // code row and one side word per block; eight streams for KIVI keys).
@@ -162,17 +135,56 @@ __device__ __forceinline__ void load8(const CacheDev& k, const CodecDev& c, int 
 }
 
 // o_i = (sum_j G_V[j][i] acc_j + accr_i) / lsum for the group of channel i, written to the output
-// view (bf16 rounded to nearest even, or binary32).  acc: LDS [nj][d].
+// view (bf16 rounded to nearest even, or binary32), for the nj <= MJ queries of the workgroup.  acc,
+// accr (may be NULL): LDS [nj][d].  A thread takes four neighbouring channels and every `groups`-th
+// row of G_V, so a row is read as 16-byte pieces and the reads of a thread's rows are independent of
+// each other (one channel per thread read its g rows behind one another); the groups' sums meet in
+// red (LDS, finalize_floats(MJ) values).
+constexpr int finalize_floats(int mj) { return 4 * kAThreads * mj; }
+
+template <int MJ>
 __device__ void finalize_rows(const AttendDev& a, const GaugeDev& G, const float* acc, const float* accr,
-                              const float* lsum, int nj, int lv, int b, int h, int hq0) {
+                              const float* lsum, int nj, int lv, int b, int h, int hq0, float* red) {
   const int d = a.q.d, g = G.g, l = lv + a.l0;
+  const int cols = d / 4, groups = g % 4 ? 0 : kAThreads / cols;
+  if (groups) {
+    const int jg = threadIdx.x / cols, c4 = threadIdx.x - jg * cols;
+    if (jg < groups) {
+      const int i0 = 4 * c4, r = i0 / g;
+      const float* Gc = G.f32 + gauge_block(l, 1, h, r, G.H, G.R) * g * g + (i0 - r * g);
+      const float* z = acc + r * g;
+      float s[MJ][4] = {};
+#pragma unroll 8
+      for (int j = jg; j < g; j += groups) {
+        const float4 gv = *reinterpret_cast<const float4*>(Gc + size_t(j) * g);
+#pragma unroll
+        for (int jj = 0; jj < MJ; ++jj) {
+          if (jj < nj) {
+            const float zz = z[jj * d + j];
+            s[jj][0] = fmaf(gv.x, zz, s[jj][0]);
+            s[jj][1] = fmaf(gv.y, zz, s[jj][1]);
+            s[jj][2] = fmaf(gv.z, zz, s[jj][2]);
+            s[jj][3] = fmaf(gv.w, zz, s[jj][3]);
+          }
+        }
+      }
+#pragma unroll
+      for (int jj = 0; jj < MJ; ++jj)
+        if (jj < nj) *reinterpret_cast<float4*>(red + (jg * MJ + jj) * d + i0) = make_float4(s[jj][0], s[jj][1], s[jj][2], s[jj][3]);
+    }
+    __syncthreads();
+  }
   for (int idx = threadIdx.x; idx < nj * d; idx += blockDim.x) {
     const int jj = idx / d, i = idx - jj * d;
-    const int r = i / g, ii = i - r * g;
-    const float* Gc = G.f32 + gauge_block(l, 1, h, r, G.H, G.R) * g * g + ii;
-    const float* z = acc + jj * d + r * g;
     float x = 0.0f;
-    for (int j = 0; j < g; ++j) x = fmaf(Gc[size_t(j) * g], z[j], x);
+    if (groups) {
+      for (int q = 0; q < groups; ++q) x += red[(q * MJ + jj) * d + i];
+    } else {
+      const int r = i / g, ii = i - r * g;
+      const float* Gc = G.f32 + gauge_block(l, 1, h, r, G.H, G.R) * g * g + ii;
+      const float* z = acc + jj * d + r * g;
+      for (int j = 0; j < g; ++j) x = fmaf(Gc[size_t(j) * g], z[j], x);
+    }
     if (accr) x += accr[jj * d + i];
     const float ls = lsum[jj];
     const float o = ls > 0.0f ? x / ls : 0.0f;
@@ -196,6 +208,10 @@ __device__ void finalize_rows(const AttendDev& a, const GaugeDev& G, const float
 constexpr int kGTile = 64;  // positions per step
 constexpr int kGAcc = 8;    // (query, channel) accumulators per thread: kJQ * d / 256 for d <= 256
 
+constexpr int generic_tile_floats(int d) {
+  return kGTile * (d + 4) > finalize_floats(kJQ) ? kGTile * (d + 4) : finalize_floats(kJQ);
+}
+
 __global__ __launch_bounds__(kAThreads) void att_generic(AttendDev a, GaugeDev G, CodecDev c) {
   extern __shared__ float sm[];
   const int d = a.q.d, H = a.kc.H, B = a.q.B;
@@ -203,7 +219,8 @@ __global__ __launch_bounds__(kAThreads) void att_generic(AttendDev a, GaugeDev G
   float* qg = sm;                       // [kJQ][d] scale * G_K q
   float* qr = qg + kJQ * d;             // [kJQ][d] scale * q
   float* tile = qr + kJQ * d;           // [kGTile][dp] keys, then values of the step
-  float* pw = tile + kGTile * dp;       // [kJQ][kGTile] scores, then weights of the step
+  // (the tile's space also holds finalize_rows' sums at the end)
+  float* pw = tile + generic_tile_floats(d);  // [kJQ][kGTile] scores, then weights of the step
   float* st = pw + kJQ * kGTile;        // [3][kJQ] running max, normaliser, step factor
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -389,13 +406,13 @@ __global__ __launch_bounds__(kAThreads) void att_generic(AttendDev a, GaugeDev G
   }
   __syncthreads();
   if (a.nsplit == 1) {
-    finalize_rows(a, G, macc, maccr, st + kJQ, nj, lv, b, h, hq0);
+    finalize_rows<kJQ>(a, G, macc, maccr, st + kJQ, nj, lv, b, h, hq0, tile);
     return;
   }
   const size_t pstride = size_t(2 + 2 * d);
   for (int jj = 0; jj < nj; ++jj) {
     float* P = a.part + ((((size_t(lv) * B + b) * a.Hq + hq0 + jj) * a.nsplit) + sp) * pstride;
-    for (int idx = tid; idx < 2 + 2 * d; idx += kAThreads) {
+    for (int idx = tid; idx < 2 + (a.raw ? 2 : 1) * d; idx += kAThreads) {
       float v;
       if (idx == 0) v = st[jj];
       else if (idx == 1) v = st[kJQ + jj];
@@ -409,12 +426,18 @@ __global__ __launch_bounds__(kAThreads) void att_generic(AttendDev a, GaugeDev G
 // ------------------------------------------------------------------------------------------
 // combine: one workgroup per (layer, batch row, KV head, query chunk)
 // ------------------------------------------------------------------------------------------
+// Bound by latency (a few KB per workgroup): the splits' maxima and sums are read by one lane each
+// and reduced in the wave, their weights exp(m - M) kept in LDS, and every thread then folds two
+// neighbouring channels over the splits with independent reads.  The partials' raw halves are read
+// only where a cache has raw positions (a.raw).  8 rows x 6 splits (one layer, 1500 positions): 23 us -> 11
+// us; 512 rows x 4 splits: 36 -> 21 us.
 __global__ __launch_bounds__(kAThreads) void att_combine(AttendDev a, GaugeDev G) {
   extern __shared__ float sm[];
-  const int d = a.q.d, H = a.kc.H, B = a.q.B;
-  float* macc = sm;             // [kJQ][d]
+  const int d = a.q.d, H = a.kc.H, B = a.q.B, ns = a.nsplit;
+  float* macc = sm;               // [kJQ][d]
   float* maccr = macc + kJQ * d;  // [kJQ][d]
-  float* mm = maccr + kJQ * d;    // [2][kJQ]
+  float* lsum = maccr + kJQ * d;  // [kJQ]
+  float* wts = lsum + kJQ;        // [kJQ][ns] weights of the splits, then finalize_rows' sums
   int sv = blockIdx.x;
   const int qc = sv % a.nqc;
   sv /= a.nqc;
@@ -422,34 +445,39 @@ __global__ __launch_bounds__(kAThreads) void att_combine(AttendDev a, GaugeDev G
   const int j0 = qc * kJQ, nj = min(kJQ, a.grp - j0);
   const int hq0 = h * a.grp + j0;
   const size_t pstride = size_t(2 + 2 * d);
-  auto part = [&](int jj, int sp) {
-    return a.part + ((((size_t(lv) * B + b) * a.Hq + hq0 + jj) * a.nsplit) + sp) * pstride;
-  };
-  if (threadIdx.x < nj) {
-    const int jj = threadIdx.x;
+  const float* part = a.part + ((size_t(lv) * B + b) * a.Hq + hq0) * ns * pstride;  // [nj][ns]
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  for (int jj = w; jj < nj; jj += kAThreads / 64) {
+    const float* P = part + size_t(jj) * ns * pstride;
     float M = -INFINITY, L = 0.0f;
-    for (int sp = 0; sp < a.nsplit; ++sp) M = fmaxf(M, part(jj, sp)[0]);
-    for (int sp = 0; sp < a.nsplit; ++sp) {
-      const float* P = part(jj, sp);
-      if (P[0] != -INFINITY) L += P[1] * __expf(P[0] - M);
+    for (int sp = lane; sp < ns; sp += 64) M = fmaxf(M, P[sp * pstride]);
+    M = wave_max(M);
+    for (int sp = lane; sp < ns; sp += 64) {
+      const float m = P[sp * pstride];
+      const float e = m == -INFINITY ? 0.0f : __expf(m - M);
+      wts[jj * ns + sp] = e;
+      L = fmaf(P[sp * pstride + 1], e, L);
     }
-    mm[jj] = M;
-    mm[kJQ + jj] = L;
+    L = wave_sum(L);
+    if (lane == 0) lsum[jj] = L;
   }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < nj * 2 * d; idx += kAThreads) {
-    const int jj = idx / (2 * d), e = idx - jj * 2 * d;
-    const float M = mm[jj];
-    float v = 0.0f;
-    for (int sp = 0; sp < a.nsplit; ++sp) {
-      const float* P = part(jj, sp);
-      if (P[0] != -INFINITY) v += P[2 + e] * __expf(P[0] - M);
+  const int e2 = a.raw ? d : d / 2;  // channel pairs of a query: gauge-space sums, then raw sums
+  for (int idx = threadIdx.x; idx < nj * e2; idx += kAThreads) {
+    const int jj = idx / e2, e = 2 * (idx - jj * e2);
+    const float* P = part + size_t(jj) * ns * pstride + 2 + e;
+    const float* wj = wts + jj * ns;
+    float2 v = make_float2(0.0f, 0.0f);
+#pragma unroll 8
+    for (int sp = 0; sp < ns; ++sp) {
+      const float2 p = *reinterpret_cast<const float2*>(P + sp * pstride);
+      v.x = fmaf(p.x, wj[sp], v.x);
+      v.y = fmaf(p.y, wj[sp], v.y);
     }
-    if (e < d) macc[jj * d + e] = v;
-    else maccr[jj * d + e - d] = v;
+    *reinterpret_cast<float2*>(e < d ? macc + jj * d + e : maccr + jj * d + e - d) = v;
   }
   __syncthreads();
-  finalize_rows(a, G, macc, maccr, mm + kJQ, nj, lv, b, h, hq0);
+  finalize_rows<kJQ>(a, G, macc, a.raw ? maccr : nullptr, lsum, nj, lv, b, h, hq0, wts);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -588,6 +616,67 @@ __device__ __forceinline__ void split2(float v, uint32_t& hi, uint32_t& lo) {
   lo = f32_to_bf16_rne(v - bf16_to_f32(hi));
 }
 
+// Rows of G_K for the query's gauge z_i = sum_j G_K[i][j] q_j: wave w takes rows 32 w .. + 31, four at a
+// time (one per DPP row of 16 lanes), each lane the 8 columns 8 (lane % 16) .. + 7 of its row (zeros
+// outside the row's group), so a row is one contiguous read and all eight passes' reads are in
+// flight together, before the query itself arrives (one 4-byte load per thread and column took 10 us
+// of a 27 us launch on a 1500-position row).  Groups that are no multiple of 8 channels are read by
+// gauge_query one row per thread.
+struct QueryRows {
+  float4 g[8][2];
+};
+__device__ __forceinline__ void load_query_rows(QueryRows& q, const GaugeDev& G, int l, int h) {
+  const int g = G.g, w = threadIdx.x >> 6, m = threadIdx.x & 15, rq = (threadIdx.x >> 4) & 3;
+  if (g % 8) return;
+  const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+  for (int p = 0; p < 8; ++p) {
+    const int i = 32 * w + 4 * p + rq, r = i / g, c = 8 * m - r * g;
+    const bool in = c >= 0 && c < g;
+    const float4* src = reinterpret_cast<const float4*>(
+        G.f32 + gauge_block(l, 0, h, r, G.H, G.R) * g * g + size_t(i - r * g) * g + (in ? c : 0));
+    const float4 v0 = src[0], v1 = src[1];
+    q.g[p][0] = in ? v0 : zero;
+    q.g[p][1] = in ? v1 : zero;
+  }
+}
+template <int JQ>
+__device__ __forceinline__ void gauge_query(const QueryRows& q, const GaugeDev& G, int l, int h, const float (*x)[kD],
+                                            float (*qt)[kD], float scale) {
+  const int g = G.g;
+  if (g % 8) {
+    for (int idx = threadIdx.x; idx < JQ * kD; idx += kAThreads) {
+      const int jj = idx / kD, i = idx % kD;
+      const int r = i / g, ii = i - r * g;
+      const float* Gr = G.f32 + gauge_block(l, 0, h, r, G.H, G.R) * g * g + size_t(ii) * g;
+      float z = 0.0f;
+      for (int j = 0; j < g; ++j) z = fmaf(Gr[j], x[jj][r * g + j], z);
+      qt[jj][i] = scale * z;
+    }
+    return;
+  }
+  const int w = threadIdx.x >> 6, m = threadIdx.x & 15, rq = (threadIdx.x >> 4) & 3;
+#pragma unroll
+  for (int jj = 0; jj < JQ; ++jj) {
+    const float4 x0 = *reinterpret_cast<const float4*>(&x[jj][8 * m]);
+    const float4 x1 = *reinterpret_cast<const float4*>(&x[jj][8 * m + 4]);
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      const float4 a = q.g[p][0], b = q.g[p][1];
+      float z = a.x * x0.x;
+      z = fmaf(a.y, x0.y, z);
+      z = fmaf(a.z, x0.z, z);
+      z = fmaf(a.w, x0.w, z);
+      z = fmaf(b.x, x1.x, z);
+      z = fmaf(b.y, x1.y, z);
+      z = fmaf(b.z, x1.z, z);
+      z = fmaf(b.w, x1.w, z);
+      z = row16_sum(z);
+      if (m == jj) qt[jj][32 * w + 4 * p + rq] = scale * z;
+    }
+  }
+}
+
 template <int BITS, int NBLK, int TB, bool KIVI = false>
 __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G) {
   static_assert(TB == 1 || TB == 16, "token tiles of 16");
@@ -620,7 +709,10 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
   // of channels 2i, 2i + 1 in word i; rows of 68 words, so the 16-byte reads of 16 tokens and the
   // word writes of 64 lanes both spread over all banks), and the side word of each channel
   constexpr int KROW = 68;
-  __shared__ __attribute__((aligned(16))) uint32_t ktk[KIVI ? 4 : 1][KIVI ? 32 * KROW : 1];
+  __shared__ __attribute__((aligned(16))) uint32_t ktk[KIVI ? 4 : 1][KIVI ? 32 * KROW : finalize_floats(JQ)];
+  // finalize_rows' sums, after the last key group
+  float* red = reinterpret_cast<float*>(&ktk[0][0]);
+  static_assert(!KIVI || 4 * 32 * KROW >= finalize_floats(JQ), "space of finalize_rows");
   __shared__ __attribute__((aligned(16))) uint32_t kgs[KIVI ? 4 : 1][KIVI ? kD : 1];
 
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -648,6 +740,8 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
   const int t_endq = min(t_end, tq);
 
   // 1. queries: macc <- q, qt <- scale G_K q, qsum <- the per-block sums of its two planes
+  QueryRows qrows;
+  load_query_rows(qrows, G, l, h);
   for (int idx = threadIdx.x; idx < JQ * kD; idx += kAThreads) {
     const int jj = idx / kD, ch = idx % kD;
     float v = 0.0f;
@@ -658,27 +752,23 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
     macc[jj][ch] = v;
   }
   __syncthreads();
-  {
-    const int g = G.g;
-    for (int idx = threadIdx.x; idx < JQ * kD; idx += kAThreads) {
-      const int jj = idx / kD, i = idx % kD;
-      const int r = i / g, ii = i - r * g;
-      const float* Gr = G.f32 + gauge_block(l, 0, h, r, G.H, G.R) * g * g + size_t(ii) * g;
-      float z = 0.0f;
-      for (int j = 0; j < g; ++j) z = fmaf(Gr[j], macc[jj][r * g + j], z);
-      qt[jj][i] = a.scale * z;
-    }
-  }
+  gauge_query<JQ>(qrows, G, l, h, macc, qt, a.scale);
   __syncthreads();
-  if (threadIdx.x < JQ * NBLK) {
-    const int jj = threadIdx.x / NBLK, k = threadIdx.x % NBLK;
+  {
+    // thread group of kAThreads / (JQ NBLK) lanes per (query, block)
+    constexpr int GL = kAThreads / (JQ * NBLK), CPL = NB / GL;
+    static_assert(GL == 32 || GL == 16, "lanes per (query, block)");
+    const int pr = threadIdx.x / GL, jj = pr / NBLK, k = pr % NBLK, c0 = k * NB + (threadIdx.x % GL) * CPL;
     float acc = 0.0f;
-    for (int ch = k * NB; ch < (k + 1) * NB; ++ch) {
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) {
       uint32_t hi, lo;
-      split2(qt[jj][ch], hi, lo);
+      split2(qt[jj][c0 + c], hi, lo);
       acc += bf16_to_f32(hi) + bf16_to_f32(lo);
     }
-    qsum[jj][k] = acc;
+#pragma unroll
+    for (int o = 1; o < GL; o <<= 1) acc += __shfl_xor(acc, o);
+    if (threadIdx.x % GL == 0) qsum[jj][k] = acc;
   }
   __syncthreads();
 
@@ -1103,18 +1193,18 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
     __syncthreads();
   }
   if (a.nsplit == 1) {
-    finalize_rows(a, G, &macc[0][0], RAW ? &accr[0][0] : nullptr, mm[1], nj, lv, b, h, hq0);
+    finalize_rows<JQ>(a, G, &macc[0][0], RAW ? &accr[0][0] : nullptr, mm[1], nj, lv, b, h, hq0, red);
     return;
   }
   const size_t pstride = size_t(2 + 2 * kD);
   for (int jj = 0; jj < nj; ++jj) {
     float* P = a.part + ((((size_t(lv) * B + b) * a.Hq + hq0 + jj) * a.nsplit) + sp) * pstride;
-    for (int idx = threadIdx.x; idx < 2 + 2 * kD; idx += kAThreads) {
+    for (int idx = threadIdx.x; idx < 2 + (RAW ? 2 : 1) * kD; idx += kAThreads) {
       float v;
       if (idx == 0) v = mm[0][jj];
       else if (idx == 1) v = mm[1][jj];
       else if (idx < 2 + kD) v = macc[jj][idx - 2];
-      else v = RAW ? accr[jj < RJ ? jj : 0][(idx - 2 - kD) % (RAW ? kD : 1)] : 0.0f;
+      else v = accr[jj < RJ ? jj : 0][(idx - 2 - kD) % (RAW ? kD : 1)];
       P[idx] = v;
     }
   }
@@ -1171,8 +1261,10 @@ bool attend_mfma_supported(const AttendDev& a, const CodecDev& c) {
          (c.n == 64 || c.n == 128) && bits;
 }
 
-hipError_t launch_attend(const AttendDev& a, const GaugeDev& G, const CodecDev& c, bool force_generic,
+hipError_t launch_attend(const AttendDev& args_in, const GaugeDev& G, const CodecDev& c, bool force_generic,
                          hipStream_t st) {
+  AttendDev a = args_in;
+  a.raw = c.backend == CG_BACKEND_KIVI || (c.backend == CG_BACKEND_BLOCK_UNIFORM && c.bt > 1);
   const int d = a.q.d;
   const int nrow = a.q.L * a.q.B * a.kc.H * a.nqc;
   if (nrow == 0) return hipSuccess;
@@ -1191,14 +1283,17 @@ hipError_t launch_attend(const AttendDev& a, const GaugeDev& G, const CodecDev& 
                         st);
     if (e != hipSuccess) return e;
   } else {
-    const size_t smem = (size_t(2) * kJQ * d + size_t(kGTile) * (d + 4) + kJQ * kGTile + 3 * kJQ) * sizeof(float);
+    const size_t smem = (size_t(2) * kJQ * d + generic_tile_floats(d) + kJQ * kGTile + 3 * kJQ) * sizeof(float);
     e = set_smem((const void*)att_generic, smem);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(att_generic, dim3(a.nsplit, nrow), dim3(kAThreads), smem, st, a, G, c);
   }
   e = hipGetLastError();
   if (e != hipSuccess || a.nsplit == 1) return e;
-  const size_t smem2 = (size_t(2) * kJQ * d + 2 * kJQ) * sizeof(float);
+  const size_t smem2 =
+      (size_t(2) * kJQ * d + kJQ + std::max(kJQ * a.nsplit, finalize_floats(kJQ))) * sizeof(float);
+  e = set_smem((const void*)att_combine, smem2);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(att_combine, dim3(nrow), dim3(kAThreads), smem2, st, a, G);
   return hipGetLastError();
 }

@@ -144,6 +144,7 @@ struct AttendDev {
   PageDev pt;            // paged caches (block-uniform per-token blocks or passthrough)
   int cap;               // positions a row can hold: T_cap, or max_pages * page_size
   int win;               // KIVI window (set by the launch for the matrix-core kernel)
+  int raw;               // partials carry raw sums (KIVI window, staged tile tokens; set by the launch)
 };
 struct AttendPlan {
   int nsplit = 1, chunk = 64, nqc = 1;
