@@ -184,6 +184,26 @@ __device__ __forceinline__ void gauge_operand(const GaugeRaw<KR, NBW>& raw, floa
     }
 }
 
+// The same operand of G^T (the inverse gauge): A[j][k] = G[4k + q][column m of block j], 16 neighbouring
+// columns of a row per 16 lanes
+template <int KR, int NBW>
+struct GaugeCols {
+  float v[NBW][KR];
+};
+template <int KR, int NBW>
+__device__ __forceinline__ void load_gauge_cols(float (&A)[NBW][KR], const GaugeDev& G, int l, int s, int h,
+                                                const WaveTile& wt) {
+  constexpr int g = 4 * KR;
+  const int lane = threadIdx.x & 63, m = lane & 15, q = lane >> 4;
+#pragma unroll
+  for (int j = 0; j < NBW; ++j) {
+    const int i0 = 16 * min(wt.cb0 + j, wt.last), r = i0 / g;
+    const float* col = G.f32 + gauge_block(l, s, h, r, G.H, G.R) * g * g + size_t(q) * g + (i0 - r * g + m);
+#pragma unroll
+    for (int kk = 0; kk < KR; ++kk) A[j][kk] = col[size_t(4 * kk) * g];
+  }
+}
+
 // out[t][i] = sum_k A_i[k] in[t][r g + k] for the wave's channel blocks and token blocks
 // tb < ntb (rows 16 ntb of both tiles are addressed)
 template <int KR, int NBW>
@@ -269,6 +289,19 @@ __device__ int quantize_block_to(const float* z, int stride, int n, int bits, ui
 // channels each (quantise_rows below); others by one thread per block.
 __device__ __host__ __forceinline__ bool lane_blocks(int n) { return n >= 8 && n <= 256 && (n & (n - 1)) == 0; }
 
+// (min, max) of a lane and the lane a DPP control brings (a lane of the same 16-lane row)
+template <int CTRL>
+__device__ __forceinline__ void lane_range(float& mn, float& mx) {
+  mn = fminf(mn, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(mn), CTRL, 0xF, 0xF, true)));
+  mx = fmaxf(mx, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(mx), CTRL, 0xF, 0xF, true)));
+}
+
+// quantize() in four instructions: the clamp to [0, qmax] (whole numbers) commutes with the rounding to
+// nearest even that v_cvt_pk_u8_f32 does
+__device__ __forceinline__ uint32_t quantize_u8(float z, float mn, float inv, float qmax) {
+  return code_u8(fminf(fmaxf(quantize_t(z, mn, inv), 0.0f), qmax));
+}
+
 // Rows [0, ntok) of a tile, bt = 1: one range per row and block of n channels (lane_blocks(n));
 // bt > 1: one range per bt rows and block (ntok a multiple of bt).  A lane takes 8 channels, the
 // lanes of a block exchange their ranges, and the 8 codes leave as `bits` bytes of the packed row
@@ -285,9 +318,15 @@ __device__ int quantise_rows(const float* zs, int ntok, int d, int dp, int n, in
   const float qmax = (float)((1 << bits) - 1);
   auto finish = [&](int t, int c8, const float (&z)[8], float mn, float mx) {
     const Side sd = make_side<true>(mn, mx, bits);
-    uint64_t acc = 0;
+    uint32_t half[2];  // four codes each (at most 32 bits)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc |= (uint64_t)quantize(z[e], sd.mn, sd.inv, qmax) << (bits * e);
+    for (int u = 0; u < 2; ++u) {
+      uint32_t q[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) q[e] = quantize_u8(z[4 * u + e], sd.mn, sd.inv, qmax);
+      half[u] = q[0] | (q[1] << bits) | ((q[2] | (q[3] << bits)) << (2 * bits));
+    }
+    const uint64_t acc = half[0] | (uint64_t(half[1]) << (4 * bits));
     uint8_t* dst = cst + (t * c8n + c8) * bits;
     switch (bits) {
       case 2: *reinterpret_cast<uint16_t*>(dst) = (uint16_t)acc; break;
@@ -323,10 +362,15 @@ __device__ int quantise_rows(const float* zs, int ntok, int d, int dp, int n, in
       mn = fminf(mn, z[e]);
       mx = fmaxf(mx, z[e]);
     }
-    // the lanes of a block are neighbours of one wave (idx is aligned to lg) and active together
-    for (int o = 1; o < lg; o <<= 1) {
-      mn = fminf(mn, __shfl_xor(mn, o));
-      mx = fmaxf(mx, __shfl_xor(mx, o));
+    // the lanes of a block are neighbours of one wave (idx is aligned to lg) and active together;
+    // once the lanes of a quad agree, a mirror of 8 (16) lanes brings the other quad's (half's) value
+    if (lg >= 2) lane_range<0xB1>(mn, mx);    // quad_perm [1,0,3,2]
+    if (lg >= 4) lane_range<0x4E>(mn, mx);    // quad_perm [2,3,0,1]
+    if (lg >= 8) lane_range<0x141>(mn, mx);   // row_half_mirror
+    if (lg >= 16) lane_range<0x140>(mn, mx);  // row_mirror
+    if (lg >= 32) {
+      mn = fminf(mn, __shfl_xor(mn, 16));
+      mx = fmaxf(mx, __shfl_xor(mx, 16));
     }
     if (bt > 1) {
       if ((c8 & (lg - 1)) == 0) red[t * nb + (c8 >> lsh)] = make_float2(mn, mx);

@@ -13,7 +13,8 @@ import oracle as O
 from paper_2607_20538_amd import codec as cg
 from paper_2607_20538_amd import synth
 
-from _parity import bf16_dev, cache_to_dev, cache_to_host, check_fused_codes, to_cg, x_dev
+from _parity import (GAUGE_TOL, bf16_dev, cache_to_dev, cache_to_host, check_bf16_within_ulp, check_fused_codes,
+                     group_rel_err, out_host, to_cg, x_dev)
 
 pytestmark = pytest.mark.gpu
 
@@ -116,3 +117,93 @@ def test_append_kivi_flush_over_group_sizes(g):
             got = cache_to_host(dev[s], oc, s)
             for key in ("codes", "side", "residual"):
                 np.testing.assert_array_equal(got[key], ref[s][key], err_msg=key)
+
+
+# (backend, bits, n, block_t): every way the encoder stores a tile and the decoder fills one
+STORES = [(O.BLOCK_UNIFORM, 4, 32, 1), (O.BLOCK_UNIFORM, 3, 32, 16), (O.KIVI, 2, 32, 1), (O.ZFP, 3, 32, 1),
+          (O.PASSTHROUGH, 8, 32, 1)]
+
+
+def _round_trip(oc, kind, L, B, H, T, d, g, dtype):
+    """Encode and decode K and V, each against the oracle."""
+    T_cap = (T + 31) // 32 * 32
+    w = _workload(L, B, H, T, d, dtype)
+    G, Gd, shp = _gauge(kind, L, H, d, g)
+    for s in (0, 1):
+        X = synth.kv_tensor(w, s)
+        ref, flags = O.kv_encode(oc, s, X, G, T_cap=T_cap)
+        dev = cg.Cache(to_cg(oc), s, L, B, H, T_cap, d)
+        err = torch.zeros(1, dtype=torch.int32, device="cuda")
+        cg.kv_encode(s, x_dev(X), Gd, shp, to_cg(oc), dev, err_flag=err)
+        torch.cuda.synchronize()
+        assert int(err.item()) == flags == 0
+        got = cache_to_host(dev, oc, s)
+        if kind == O.GAUGE_IDENTITY:
+            for key in ("codes", "side", "residual"):
+                if got[key] is not None:
+                    np.testing.assert_array_equal(got[key], ref[key], err_msg=key)
+        elif oc.backend == O.PASSTHROUGH:
+            assert group_rel_err(ref["codes"], got["codes"], g) <= GAUGE_TOL
+        elif oc.backend != O.ZFP:
+            z, _ = O.kv_encode(O.Codec(backend=O.PASSTHROUGH), s, X, G, T_cap=T_cap)
+            tq = O.kivi_tq(T, oc) if oc.backend == O.KIVI else O.tile_tq(T, oc)
+            check_fused_codes(got, ref, z["codes"], oc, s, d, tq)
+        # decode of the oracle's cache, from the start and from an offset
+        cache = cache_to_dev(ref, oc, s, L, B, H, T_cap, d, len_=T)
+        for t0 in (0, 36):
+            want = O.kv_decode(oc, s, G, ref, t0, T - t0, lens=np.full(B, T, np.int32), out_bf16=False)
+            for dt in (torch.float32, torch.bfloat16):
+                Y = torch.zeros((L, B, H, T - t0, d), dtype=dt, device="cuda")
+                cg.kv_decode(s, cache, Gd, shp, to_cg(oc), t0, Y, err_flag=err)
+                torch.cuda.synchronize()
+                if dt == torch.float32:
+                    assert group_rel_err(want, Y.cpu().numpy(), g) <= GAUGE_TOL
+                else:
+                    check_bf16_within_ulp(want, out_host(Y), g)
+        assert int(err.item()) == 0
+
+
+@pytest.mark.parametrize("kind", [O.GAUGE_IDENTITY, O.GAUGE_HAAR], ids=["identity", "haar"])
+@pytest.mark.parametrize("backend,bits,n,bt", STORES)
+@pytest.mark.parametrize("d,g", [(32, 32), (64, 64), (64, 8), (96, 96), (96, 48), (192, 192), (256, 256)])
+def test_round_trip_over_head_widths(d, g, backend, bits, n, bt, kind):
+    """A ragged last tile, offsets inside a tile, window and staged rows."""
+    oc = O.Codec(backend=backend, bits=bits, block_c=n, key_tokens=32, val_channels=n, residual=32, block_t=bt)
+    T = 204 if backend == O.ZFP else 205
+    _round_trip(oc, kind, 1, 2, 2, T, d, g, "bf16" if backend == O.KIVI or bt > 1 or d == 96 else "f32")
+
+
+@pytest.mark.parametrize("d,g,bits,n", [(64, 64, 4, 32), (80, 80, 4, 80), (64, 16, 6, 16), (48, 16, 2, 16)])
+def test_round_trip_with_several_tiles_per_workgroup(d, g, bits, n):
+    """Enough tokens that a workgroup runs several 64-token tiles, the next one fetched ahead."""
+    oc = O.Codec(backend=O.BLOCK_UNIFORM, bits=bits, block_c=n)
+    _round_trip(oc, O.GAUGE_IDENTITY, 2, 2, 16, 64 * 34 + 5, d, g, "bf16")
+
+
+def test_round_trip_of_64_token_key_groups():
+    """Tiles of more granules than a thread fetches ahead (64 tokens of 256 channels)."""
+    oc = O.Codec(backend=O.KIVI, bits=4, key_tokens=64, val_channels=64, residual=64)
+    _round_trip(oc, O.GAUGE_IDENTITY, 1, 1, 2, 64 * 5 + 33, 256, 64, "bf16")
+
+
+def test_general_encoder_flags_and_keeps_neighbouring_groups():
+    """A non-finite channel sets NONFINITE and leaves every other group's codes alone."""
+    d, g, T = 64, 16, 64
+    oc = cg.Codec(cg.BLOCK_UNIFORM, 4, 16)
+    _, Gd, shp = _gauge(O.GAUGE_HAAR, 1, 1, d, g)
+    X = torch.randn((1, 1, 1, T, d), device="cuda")
+    caches = []
+    for bad in (None, float("nan"), float("inf")):
+        x = X.clone()
+        if bad is not None:
+            x[0, 0, 0, 33, 20] = bad
+        k = cg.Cache(oc, 0, 1, 1, 1, T, d)
+        err = torch.zeros(1, dtype=torch.int32, device="cuda")
+        cg.kv_encode(0, x, Gd, shp, oc, k, err_flag=err)
+        torch.cuda.synchronize()
+        assert bool(int(err.item()) & cg.CG_FLAG_NONFINITE) == (bad is not None)
+        caches.append((k.codes.view(T, 4, 8).clone(), k.side.view(T, 4, 4).clone()))
+    keep = torch.ones((T, 4), dtype=torch.bool, device="cuda")
+    keep[33, 1] = False
+    for codes, side in caches[1:]:
+        assert torch.equal(codes[keep], caches[0][0][keep]) and torch.equal(side[keep], caches[0][1][keep])
