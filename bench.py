@@ -58,7 +58,7 @@ def kernel_source_hash():
     import hashlib
 
     h = hashlib.sha256()
-    for f in ("cg_mfma.hip", "cg_mfma_util.h"):
+    for f in ("cg_mfma.hip", "cg_mfma_enc.hip", "cg_mfma_common.h", "cg_mfma_util.h"):
         h.update(open(os.path.join(ROOT, "paper_2607_20538_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 

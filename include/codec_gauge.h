@@ -346,7 +346,7 @@ int32_t kv_attend_paged(int32_t l0, int32_t l1, const cg_kv_view* q, const cg_ca
 /* Encode into paged caches: Z = G X, B_c = C(Z) (section 3) for the X->T tokens of every batch
  * row b of X (shape [L][B][H][T][d]), written at row b's positions [t0, t0 + X->T), i.e. into
  * the pool pages the table assigns to them.  t0 % 32 == 0; block-uniform with block_t = 1, or
- * passthrough; runs on the general kernels.  Positions past the table or pages outside the
+ * passthrough.  Positions past the table or pages outside the
  * pool set CG_FLAG_POS_RANGE and skip that 32-position tile.  Errors: as kv_encode. */
 int32_t kv_encode_paged(int32_t s, const cg_kv_view* X, const cg_page_table* pages, const void* G_dev,
                         cg_gauge_shape shp, const cg_codec* codec, const cg_cache* out, int32_t t0, int32_t* err_flag,

@@ -381,9 +381,10 @@ static bool force_generic() {
 }
 
 hipError_t launch_encode(int s, const ViewDev& X, int l0, const GaugeDev& G, const CodecDev& c, const CacheDev& k,
-                         int t0, int tq, int* err, hipStream_t st) {
-  if (!force_generic() && mfma_encode_supported(X, G, c)) return launch_encode_mfma(s, X, l0, G, c, k, t0, tq, err, st);
-  return launch_encode_generic(s, X, l0, G, c, k, t0, tq, err, st);
+                         int t0, int tq, int* err, hipStream_t st, const PageDev& pt) {
+  if (!force_generic() && mfma_encode_supported(X, G, c, pt.pages != nullptr))
+    return launch_encode_mfma(s, X, l0, G, c, k, t0, tq, err, st, pt);
+  return launch_encode_generic(s, X, l0, G, c, k, t0, tq, err, st, pt);
 }
 
 hipError_t launch_decode(int s, const CacheDev& k, int l0, const GaugeDev& G, const CodecDev& c, int t0, int len,
@@ -854,8 +855,8 @@ int32_t kv_encode_paged(int32_t s, const cg_kv_view* X, const cg_page_table* pag
   pt.pages = pages->pages;
   pt.max_pages = pages->max_pages;
   pt.page_size = pages->page_size;
-  hipError_t e = launch_encode_generic(s, view_dev(X), 0, gauge_dev(G_dev, shp), codec_dev(codec), cache_dev(out), t0,
-                                       X->T, err_flag, static_cast<hipStream_t>(stream), pt);
+  hipError_t e = launch_encode(s, view_dev(X), 0, gauge_dev(G_dev, shp), codec_dev(codec), cache_dev(out), t0, X->T,
+                               err_flag, static_cast<hipStream_t>(stream), pt);
   return e == hipSuccess ? CG_OK : CG_ERR_DEVICE;
 }
 

@@ -101,10 +101,11 @@ hipError_t launch_decode_generic(int s, const CacheDev& k, int l0, const GaugeDe
                                  int len, const int* pos, int pos_add, const ViewDev& Y, int* err, hipStream_t st);
 
 // Matrix-core kernels: bf16, head dimension 128, block-uniform (n in {16, 32, 64}) or passthrough.
-bool mfma_encode_supported(const ViewDev& X, const GaugeDev& G, const CodecDev& c);
+bool mfma_encode_supported(const ViewDev& X, const GaugeDev& G, const CodecDev& c, bool paged = false);
 bool mfma_decode_supported(int s, const ViewDev& Y, const GaugeDev& G, const CodecDev& c);
 hipError_t launch_encode_mfma(int s, const ViewDev& X, int l0, const GaugeDev& G, const CodecDev& c,
-                              const CacheDev& k, int t0, int tq, int* err, hipStream_t st);
+                              const CacheDev& k, int t0, int tq, int* err, hipStream_t st,
+                              const PageDev& pt = PageDev());
 hipError_t launch_decode_mfma(int s, const CacheDev& k, int l0, const GaugeDev& G, const CodecDev& c, int t0,
                               int len, const int* pos, int pos_add, const ViewDev& Y, int* err, hipStream_t st);
 
@@ -171,7 +172,7 @@ hipError_t launch_selftest(int which, unsigned long long* bad, hipStream_t st);
 // Encode tokens [0, X.T) of view X into cache positions [t0, t0 + X.T); layer l of the view is
 // cache layer l + l0.  tq: KIVI / tile tokens to quantise (others go to the window).
 hipError_t launch_encode(int s, const ViewDev& X, int l0, const GaugeDev& G, const CodecDev& c, const CacheDev& k,
-                         int t0, int tq, int* err, hipStream_t st);
+                         int t0, int tq, int* err, hipStream_t st, const PageDev& pt = PageDev());
 // Decode cache positions [t0, t0 + Y.T) into view Y (layer l of Y is cache layer l + l0).
 // If pos is non-NULL, batch row b holds pos[b] + pos_add tokens (a rolling step passes its
 // positions with pos_add = 1, kv_decode its per-row lengths with pos_add = 0) and only the
