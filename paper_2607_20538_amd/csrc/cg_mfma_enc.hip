@@ -390,7 +390,10 @@ __global__ __launch_bounds__(kThreads, NP == 2 ? 3 : 2) void enc_mfma(MfmaArgs a
         }
       }
 #pragma unroll
-      for (int i = 0; i < BITS; ++i) words[i] |= __shfl_xor(words[i], 32);
+      for (int i = 0; i < BITS; ++i) {  // both half-waves' patterns (v_permlane32_swap: own and partner's)
+        const auto u = __builtin_amdgcn_permlane32_swap(words[i], words[i], false, false);
+        words[i] = u[0] | u[1];
+      }
 #pragma unroll
       for (int i = 0; i < BITS; ++i) asm volatile("" ::"v"(words[i]));
       asm volatile("" ::"v"(sd.word));
@@ -457,20 +460,16 @@ __global__ __launch_bounds__(kThreads, NP == 2 ? 3 : 2) void enc_mfma(MfmaArgs a
         if constexpr (BITS == 6) {
           pack16<BITS>(q, words);
         } else {
-          // 16 odd-width codes span 1.5 words: the lane pair of a token packs its 32 codes
-          // (BITS words) together and the lower half stores them
-          uint32_t hq[16];
-#pragma unroll
-          for (int e = 0; e < 16; ++e) hq[e] = __shfl_xor(q[e], 32);
-#pragma unroll
-          for (int i = 0; i < BITS; ++i) words[i] = 0;
-#pragma unroll
-          for (int e = 0; e < 32; ++e) {
-            const uint32_t v = e < 16 ? q[e] : hq[e - 16];
-            const int bit = e * BITS, wd = bit >> 5, off = bit & 31;
-            words[wd] |= v << off;
-            if (off + BITS > 32) words[wd + 1] |= v >> (32 - off);
-          }
+          // 16 odd-width codes span 1.5 words: the lane packs its own 16, the upper half-wave's words
+          // cross over (v_permlane32_swap), and the lower half joins and stores the 32 codes' BITS words
+          static_assert(BITS == 3, "odd widths");
+          uint32_t own[2];
+          pack16<BITS>(q, own);
+          const auto u0 = __builtin_amdgcn_permlane32_swap(own[0], own[0], false, false);
+          const auto u1 = __builtin_amdgcn_permlane32_swap(own[1], own[1], false, false);
+          words[0] = own[0];
+          words[1] = own[1] | (u0[1] << 16);
+          words[2] = (u0[1] >> 16) | (u1[1] << 16);
         }
       }
       // keep the epilogue in this block (not sunk into the store branch) so the scheduler can
