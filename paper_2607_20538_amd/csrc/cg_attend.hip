@@ -554,6 +554,13 @@ __device__ __forceinline__ void vchunk(uint32_t w0, uint32_t w1, uint32_t sh, ui
   }
 }
 
+// Byte of a 32-bit word from which 16 bits hold the b-bit code at bit off (off + b <= 32): the lowest
+// even byte where that works, so that neighbouring codes share the window, else the code's own byte.
+constexpr int kivi_window(int off, int b) {
+  const int e = (off >> 4) * 2;
+  return off - 8 * e + b <= 16 ? e : off >> 3;
+}
+
 // Value B fragment of N-tile k: code k of the 8 tokens' chunks as bf16 1 + q 2^-BITS (8 bits: q
 // itself), token pair (2i, 2i + 1) in dword i.  4 and 6 bits: one byte permute puts the two
 // tokens' bytes holding code k 16 bits apart, one shift aligns the code with the mantissa.
@@ -589,6 +596,16 @@ __device__ __forceinline__ bf16x8_t vfrag(const uint32_t (&lo)[8], const uint32_
       // the code sits at bit r of each half: move it to mantissa bits 1..6
       const uint32_t y = r >= 1 ? (x >> (r - 1)) : (x << 1);
       f[i] = (y & 0x007E007Eu) | one;
+    } else if constexpr (BITS == 2 || BITS == 3) {
+      // the 8 codes fill bytes 0..1 (2 bits) or 0..2 of lo: a permute puts a 16-bit window of both
+      // tokens' chunks into the halves (byte 0 up to code 7 or 4, byte 1 for codes 5..7 of 3 bits),
+      // one shift moves the code to the mantissa's top bits
+      constexpr int P = 7 - BITS;
+      constexpr uint32_t FM = (((1u << BITS) - 1u) << P) * 0x00010001u;
+      const uint32_t o = BITS == 3 && k >= 5 ? 1u : 0u;
+      const int r = BITS * k - 8 * int(o);  // bit of the code in its half, at most 14
+      const uint32_t x = __builtin_amdgcn_perm(a1, a0, o | ((o + 1) << 8) | ((o + 4) << 16) | ((o + 5) << 24));
+      f[i] = ((r >= P ? x >> (r - P) : x << (P - r)) & FM) | one;
     } else {
       const uint64_t c0w = (uint64_t(hi[2 * i]) << 32) | a0, c1w = (uint64_t(hi[2 * i + 1]) << 32) | a1;
       const uint32_t c0 = uint32_t(c0w >> (BITS * k)) & M, c1 = uint32_t(c1w >> (BITS * k)) & M;
@@ -698,10 +715,10 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
   __shared__ float offs[4][16][4];
   __shared__ float ml[4][2][JQ];
   __shared__ float mm[2][JQ];
-  // raw positions (staged tile tokens, the KIVI window): scores then weights of a chunk of 16,
+  // raw positions (staged tile tokens, the KIVI window): scores then weights of a chunk of 64,
   // running maximum and sum per query, the chunk's rescaling factor, value sums
   constexpr int RJ = RAW ? JQ : 1;
-  __shared__ float rs[RJ][16];
+  __shared__ float rs[RJ][64];
   __shared__ float rml[2][RJ];
   __shared__ float rfac[RJ];
   __shared__ __attribute__((aligned(16))) float accr[RJ][RAW ? kD : 1];
@@ -800,12 +817,15 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
   const int jw = n / (2 * NBLK), bw = (n / 2) % NBLK, pw = n & 1;
   // KIVI score rows use the same (query, block, plane) mapping: row n holds qt of its query at the
   // 16 channels 64 bw + 32 v + 8 gq + i (K-steps 2 bw + v), zero at the other K-steps
-  float qk[KIVI ? 16 : 1];
+  float qk[KIVI ? 16 : 1], qm[KIVI ? 16 : 1];
   if constexpr (KIVI) {
 #pragma unroll
     for (int v = 0; v < 2; ++v)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) qk[8 * v + i] = qt[jw][64 * bw + 32 * v + 8 * gq + i];
+      for (int i = 0; i < 8; ++i) {
+        qk[8 * v + i] = qt[jw][64 * bw + 32 * v + 8 * gq + i];
+        qm[8 * v + i] = pw == 0 ? qk[8 * v + i] * (1.0f / kSK2) : 0.0f;
+      }
   }
 
   float mrun[NQL], lp[NQL];
@@ -893,7 +913,6 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
       // the group to the wave's LDS region: this lane's two channel streams (words 0 .. BITS - 1
       // of channel 2 lane, then those of channel 2 lane + 1) become, for every token t, the bf16
       // pair of B values of the two channels: 1 + q 2^-b (8 bits: q)
-      constexpr uint32_t QM = (1u << BITS) - 1u;
       uint32_t sw2[2 * BITS];
 #pragma unroll
       for (int i = 0; i < BITS; ++i) {
@@ -903,18 +922,29 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
 #pragma unroll
       for (int t = 0; t < 32; ++t) {
         const int bit = t * BITS, wd = bit >> 5, off = bit & 31;
-        uint32_t qa, qb;
-        if (off + BITS <= 32) {
-          qa = (sw2[wd] >> off) & QM;
-          qb = (sw2[BITS + wd] >> off) & QM;
+        if constexpr (BITS == 8) {
+          const uint32_t qa = (sw2[wd] >> off) & 0xffu, qb = (sw2[BITS + wd] >> off) & 0xffu;
+          ktk[w][t * KROW + lane] = __builtin_amdgcn_perm(__float_as_uint(float(qb)), __float_as_uint(float(qa)), 0x07060302u);
         } else {
-          qa = __builtin_amdgcn_alignbit(sw2[wd + 1], sw2[wd], off) & QM;
-          qb = __builtin_amdgcn_alignbit(sw2[BITS + wd + 1], sw2[BITS + wd], off) & QM;
+          // the two channels' codes to the halves of one word: a permute of the bytes holding them (a
+          // 16-bit window, shared by the codes it holds; codes that straddle words are aligned
+          // first), then one shift to the mantissa's top bits
+          constexpr int P = 7 - BITS;
+          constexpr uint32_t FM = (((1u << BITS) - 1u) << P) * 0x00010001u;
+          uint32_t x;
+          int r;
+          if (off + BITS <= 32) {
+            const int o = kivi_window(off, BITS);
+            r = off - 8 * o;
+            const uint32_t o0 = uint32_t(o), o1 = uint32_t(o < 3 ? o + 1 : o);
+            x = __builtin_amdgcn_perm(sw2[BITS + wd], sw2[wd], o0 | (o1 << 8) | ((o0 + 4) << 16) | ((o1 + 4) << 24));
+          } else {
+            r = 0;
+            x = __builtin_amdgcn_perm(__builtin_amdgcn_alignbit(sw2[BITS + wd + 1], sw2[BITS + wd], off),
+                                      __builtin_amdgcn_alignbit(sw2[wd + 1], sw2[wd], off), 0x05040100u);
+          }
+          ktk[w][t * KROW + lane] = ((r >= P ? x >> (r - P) : x << (P - r)) & FM) | one;
         }
-        uint32_t pr;
-        if constexpr (BITS == 8) pr = __builtin_amdgcn_perm(__float_as_uint(float(qb)), __float_as_uint(float(qa)), 0x07060302u);
-        else pr = one | (qa << (7 - BITS)) | (qb << (23 - BITS));
-        ktk[w][t * KROW + lane] = pr;
       }
       *reinterpret_cast<uint2*>(&kgs[w][2 * lane]) = ksv;
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -940,15 +970,12 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
           const float x0 = q0 * f16_bits_to_f32(se[2 * e2] >> 16), x1 = q1 * f16_bits_to_f32(se[2 * e2 + 1] >> 16);
           const uint32_t hi = pk_bf16(x0, x1);
           const float h0 = __uint_as_float(hi << 16), h1 = __uint_as_float(hi & 0xffff0000u);
-          const uint32_t lo = pk_bf16(x0 - h0, x1 - h1);
-          fa[v][e2] = pw ? lo : hi;
-          if (pw == 0) {
-            part = fmaf(q0, f16_bits_to_f32(se[2 * e2] & 0xffffu) * (1.0f / kSK2), part);
-            part = fmaf(q1, f16_bits_to_f32(se[2 * e2 + 1] & 0xffffu) * (1.0f / kSK2), part);
-            if constexpr (BITS != 8) part -= h0 + h1;
-          } else if constexpr (BITS != 8) {
-            part -= __uint_as_float(lo << 16) + __uint_as_float(lo & 0xffff0000u);
-          }
+          const uint32_t pl = pw ? pk_bf16(x0 - h0, x1 - h1) : hi;
+          fa[v][e2] = pl;
+          // (qm is qt / k on plane-0 rows and 0 on the others)
+          part = fmaf(qm[8 * v + 2 * e2], f16_bits_to_f32(se[2 * e2] & 0xffffu), part);
+          part = fmaf(qm[8 * v + 2 * e2 + 1], f16_bits_to_f32(se[2 * e2 + 1] & 0xffffu), part);
+          if constexpr (BITS != 8) part -= __uint_as_float(pl << 16) + __uint_as_float(pl & 0xffff0000u);
         }
       }
       const u32x4_t zero4 = {0u, 0u, 0u, 0u};
@@ -1065,57 +1092,113 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
   for (; t0 + 32 <= t_endq; t0 += 128) step(t0, std::true_type{});
   if (t0 < t_endq) step(t0, std::false_type{});
 
-  // raw positions [max(tq, t_begin), t_end) of this split (staged tile tokens, at most 15; the
-  // KIVI window, at most win + 31), in chunks of 16: scores with the raw query (macc still holds
-  // q), a running maximum and sum per query, raw value sums rescaled as the maximum moves
+  // raw positions [max(tq, t_begin), t_end) of this split (staged tile tokens, at most 15; the KIVI
+  // window, at most win + 31), 64 at a time: 16 lanes read a position's key row and share its
+  // scores with the raw query (macc still holds q), a wave keeps the running maximum and sum of a
+  // query, and each thread folds 8 channels of every 16th position's value row, rescaled as the
+  // maximum moves.  One workgroup per row has them all, so their latency adds to the launch: with
+  // one thread per position reading its row 2 bytes at a time, the 128 to 159 positions of a KIVI window
+  // were 146 of a 380 us launch (8 layers x 4 rows x 8 heads x 16000 positions, 3 bits).
   if constexpr (RAW) {
     const int ringsz = KIVI ? a.win + 32 : TB;
     const int r0 = max(tq, t_begin), nr = max(0, t_end - r0);
-    const size_t slc = (size_t(l) * a.kc.B + b) * a.kc.H + h;
+    const size_t ring0 = ((size_t(l) * a.kc.B + b) * a.kc.H + h) * ringsz;
     if (threadIdx.x < RJ) {
       rml[0][threadIdx.x] = -INFINITY;
       rml[1][threadIdx.x] = 0.0f;
     }
-    for (int idx = threadIdx.x; idx < RJ * kD; idx += kAThreads) (&accr[0][0])[idx] = 0.0f;
-    for (int c0 = 0; c0 < nr; c0 += 16) {
-      const int nc = min(16, nr - c0);
-      __syncthreads();
-      if (threadIdx.x < JQ * 16) {
-        const int jj = threadIdx.x / 16, r = threadIdx.x % 16;
-        float sc = -INFINITY;
-        if (jj < nj && r < nc) {
-          const uint16_t* kr = a.kc.ring + (slc * ringsz + (r0 + c0 + r) % ringsz) * kD;
-          float acc = 0.0f;
-          for (int ch = 0; ch < kD; ++ch) acc = fmaf(macc[jj][ch], bf16_to_f32(kr[ch]), acc);
-          sc = a.scale * acc;
+    if (nr > 0) {
+      float qv[JQ][8], va[JQ][8];
+#pragma unroll
+      for (int jj = 0; jj < JQ; ++jj)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          qv[jj][e] = macc[jj][8 * n + e];
+          va[jj][e] = 0.0f;
         }
-        rs[jj][r] = sc;
-      }
-      __syncthreads();
-      if (threadIdx.x < JQ) {
-        const int jj = threadIdx.x;
-        const float mo = rml[0][jj];
-        float m = mo;
-        for (int r = 0; r < nc; ++r) m = fmaxf(m, rs[jj][r]);
-        const float f = mo == -INFINITY ? 0.0f : __expf(mo - m);
-        float sum = rml[1][jj] * f;
-        for (int r = 0; r < nc; ++r) {
-          const float pr = m == -INFINITY ? 0.0f : __expf(rs[jj][r] - m);
-          rs[jj][r] = pr;
-          sum += pr;
+      auto row8 = [](const uint16_t* ring, size_t row, int c8) {
+        return *reinterpret_cast<const uint4*>(ring + row * kD + 8 * c8);
+      };
+      auto lo_hi = [](const uint4& v, float (&x)[8]) {
+        const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          x[2 * e] = __uint_as_float(u[e] << 16);
+          x[2 * e + 1] = __uint_as_float(u[e] & 0xffff0000u);
         }
-        rml[0][jj] = m;
-        rml[1][jj] = sum;
-        rfac[jj] = f;
+      };
+      for (int c0 = 0; c0 < nr; c0 += 64) {
+        const int nc = min(64, nr - c0);
+        // positions 16 w + 4 i + gq of the chunk for the scores, 16 i + 4 w + gq for the values
+        uint4 kr[4], vr[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          kr[i] = row8(a.kc.ring, ring0 + (r0 + c0 + min(16 * w + 4 * i + gq, nc - 1)) % ringsz, n);
+          vr[i] = row8(a.vc.ring, ring0 + (r0 + c0 + min(16 * i + 4 * w + gq, nc - 1)) % ringsz, n);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float x[8];
+          lo_hi(kr[i], x);
+          const int r = 16 * w + 4 * i + gq;
+#pragma unroll
+          for (int jj = 0; jj < JQ; ++jj) {
+            float z = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) z = fmaf(qv[jj][e], x[e], z);
+            z = row16_sum(z);
+            if (n == jj) rs[jj][r] = jj < nj && r < nc ? a.scale * z : -INFINITY;
+          }
+        }
+        __syncthreads();
+        for (int jj = w; jj < JQ; jj += 4) {
+          const float sc = rs[jj][lane], mo = rml[0][jj];
+          const float m = fmaxf(mo, wave_max(sc));
+          const float p = sc == -INFINITY ? 0.0f : __expf(sc - m);
+          const float f = mo == -INFINITY ? 0.0f : __expf(mo - m);
+          const float sum = wave_sum(p);
+          rs[jj][lane] = p;
+          if (lane == 0) {
+            rml[0][jj] = m;
+            rml[1][jj] = fmaf(rml[1][jj], f, sum);
+            rfac[jj] = f;
+          }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int jj = 0; jj < JQ; ++jj) {
+          const float f = rfac[jj];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) va[jj][e] *= f;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float x[8];
+          lo_hi(vr[i], x);
+#pragma unroll
+          for (int jj = 0; jj < JQ; ++jj) {
+            const float p = rs[jj][16 * i + 4 * w + gq];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) va[jj][e] = fmaf(p, x[e], va[jj][e]);
+          }
+        }
       }
+      // the four lane rows' sums, then the four waves' (red is free: every wave has passed the barriers)
+#pragma unroll
+      for (int jj = 0; jj < JQ; ++jj)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          float v = va[jj][e];
+          v += __shfl_xor(v, 16);
+          v += __shfl_xor(v, 32);
+          if (gq == 0) red[(w * JQ + jj) * kD + 8 * n + e] = v;
+        }
       __syncthreads();
-      for (int idx = threadIdx.x; idx < JQ * kD; idx += kAThreads) {
-        const int jj = idx / kD, ch = idx % kD;
-        float acc = accr[jj][ch] * rfac[jj];
-        for (int r = 0; r < nc; ++r)
-          acc = fmaf(rs[jj][r], bf16_to_f32(a.vc.ring[(slc * ringsz + (r0 + c0 + r) % ringsz) * kD + ch]), acc);
-        accr[jj][ch] = acc;
-      }
+      for (int idx = threadIdx.x; idx < JQ * kD; idx += kAThreads)
+        (&accr[0][0])[idx] = (red[idx] + red[JQ * kD + idx]) + (red[2 * JQ * kD + idx] + red[3 * JQ * kD + idx]);
+    } else {
+      for (int idx = threadIdx.x; idx < RJ * kD; idx += kAThreads) (&accr[0][0])[idx] = 0.0f;
     }
   }
 
