@@ -136,44 +136,70 @@ __device__ __forceinline__ void load8(const CacheDev& k, const CodecDev& c, int 
 
 // o_i = (sum_j G_V[j][i] acc_j + accr_i) / lsum for the group of channel i, written to the output
 // view (bf16 rounded to nearest even, or binary32), for the nj <= MJ queries of the workgroup.  acc,
-// accr (may be NULL): LDS [nj][d].  A thread takes four neighbouring channels and every `groups`-th
-// row of G_V, so a row is read as 16-byte pieces and the reads of a thread's rows are independent of
-// each other (one channel per thread read its g rows behind one another); the groups' sums meet in
-// red (LDS, finalize_floats(MJ) values).
+// accr (may be NULL): LDS [MJ][d].  A thread takes four neighbouring channels and an equal share of
+// the rows of G_V, read as 16-byte pieces that do not depend on the sums: load_out_rows issues them early
+// (behind one another, after the sums, they were 7 of a 10 us combine).  The shares' sums meet in red
+// (LDS, finalize_floats(MJ) values).  Wider gauges (g d > 16 K entries) are read in the loop, and
+// groups that are no multiple of 4 channels one column per thread.
 constexpr int finalize_floats(int mj) { return 4 * kAThreads * mj; }
+constexpr int kOutRows = 16;  // rows of G_V a thread holds
+
+struct OutRows {
+  float4 v[kOutRows];
+  int i0, jg, rows, groups;  // first channel, share, rows per share, shares (0: not split)
+};
+__device__ __forceinline__ void load_out_rows(OutRows& o, const GaugeDev& G, int d, int l, int h) {
+  const int g = G.g, cols = d / 4;
+  o.groups = g % 4 ? 0 : kAThreads / cols;
+  o.jg = threadIdx.x / cols;
+  o.i0 = 4 * (threadIdx.x - o.jg * cols);
+  o.rows = o.groups ? (g + o.groups - 1) / o.groups : 0;
+  if (!o.groups || o.jg >= o.groups || o.rows > kOutRows) return;
+  const int r = o.i0 / g, j0 = o.jg * o.rows;
+  const float* Gc = G.f32 + gauge_block(l, 1, h, r, G.H, G.R) * g * g + (o.i0 - r * g);
+#pragma unroll
+  for (int q = 0; q < kOutRows; q += 4) {
+    if (q < o.rows) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        o.v[q + u] = *reinterpret_cast<const float4*>(Gc + size_t(min(j0 + q + u, g - 1)) * g);
+    }
+  }
+}
 
 template <int MJ>
-__device__ void finalize_rows(const AttendDev& a, const GaugeDev& G, const float* acc, const float* accr,
-                              const float* lsum, int nj, int lv, int b, int h, int hq0, float* red) {
-  const int d = a.q.d, g = G.g, l = lv + a.l0;
-  const int cols = d / 4, groups = g % 4 ? 0 : kAThreads / cols;
-  if (groups) {
-    const int jg = threadIdx.x / cols, c4 = threadIdx.x - jg * cols;
-    if (jg < groups) {
-      const int i0 = 4 * c4, r = i0 / g;
-      const float* Gc = G.f32 + gauge_block(l, 1, h, r, G.H, G.R) * g * g + (i0 - r * g);
-      const float* z = acc + r * g;
-      float s[MJ][4] = {};
-#pragma unroll 8
-      for (int j = jg; j < g; j += groups) {
-        const float4 gv = *reinterpret_cast<const float4*>(Gc + size_t(j) * g);
+__device__ void finalize_rows(const AttendDev& a, const GaugeDev& G, const OutRows& out, const float* acc,
+                              const float* accr, const float* lsum, int nj, int lv, int b, int h, int hq0,
+                              float* red) {
+  const int d = a.q.d, g = G.g, l = lv + a.l0, groups = out.groups;
+  if (groups && out.jg < groups) {
+    const int r = out.i0 / g, j0 = out.jg * out.rows, j1 = min(g, j0 + out.rows);
+    const float* z = acc + r * g;
+    float s[MJ][4] = {};
+    auto row = [&](int j, const float4& gv) {
 #pragma unroll
-        for (int jj = 0; jj < MJ; ++jj) {
-          if (jj < nj) {
-            const float zz = z[jj * d + j];
-            s[jj][0] = fmaf(gv.x, zz, s[jj][0]);
-            s[jj][1] = fmaf(gv.y, zz, s[jj][1]);
-            s[jj][2] = fmaf(gv.z, zz, s[jj][2]);
-            s[jj][3] = fmaf(gv.w, zz, s[jj][3]);
-          }
-        }
+      for (int jj = 0; jj < MJ; ++jj) {
+        const float zz = z[jj * d + j];
+        s[jj][0] = fmaf(gv.x, zz, s[jj][0]);
+        s[jj][1] = fmaf(gv.y, zz, s[jj][1]);
+        s[jj][2] = fmaf(gv.z, zz, s[jj][2]);
+        s[jj][3] = fmaf(gv.w, zz, s[jj][3]);
       }
+    };
+    if (out.rows <= kOutRows) {
 #pragma unroll
-      for (int jj = 0; jj < MJ; ++jj)
-        if (jj < nj) *reinterpret_cast<float4*>(red + (jg * MJ + jj) * d + i0) = make_float4(s[jj][0], s[jj][1], s[jj][2], s[jj][3]);
+      for (int q = 0; q < kOutRows; ++q)
+        if (j0 + q < j1) row(j0 + q, out.v[q]);
+    } else {
+      const float* Gc = G.f32 + gauge_block(l, 1, h, r, G.H, G.R) * g * g + (out.i0 - r * g);
+#pragma unroll 8
+      for (int j = j0; j < j1; ++j) row(j, *reinterpret_cast<const float4*>(Gc + size_t(j) * g));
     }
-    __syncthreads();
+#pragma unroll
+    for (int jj = 0; jj < MJ; ++jj)
+      *reinterpret_cast<float4*>(red + (out.jg * MJ + jj) * d + out.i0) = make_float4(s[jj][0], s[jj][1], s[jj][2], s[jj][3]);
   }
+  __syncthreads();
   for (int idx = threadIdx.x; idx < nj * d; idx += blockDim.x) {
     const int jj = idx / d, i = idx - jj * d;
     float x = 0.0f;
@@ -406,7 +432,9 @@ __global__ __launch_bounds__(kAThreads) void att_generic(AttendDev a, GaugeDev G
   }
   __syncthreads();
   if (a.nsplit == 1) {
-    finalize_rows<kJQ>(a, G, macc, maccr, st + kJQ, nj, lv, b, h, hq0, tile);
+    OutRows out;
+    load_out_rows(out, G, d, l, h);
+    finalize_rows<kJQ>(a, G, out, macc, maccr, st + kJQ, nj, lv, b, h, hq0, tile);
     return;
   }
   const size_t pstride = size_t(2 + 2 * d);
@@ -429,8 +457,8 @@ __global__ __launch_bounds__(kAThreads) void att_generic(AttendDev a, GaugeDev G
 // Bound by latency (a few KB per workgroup): the splits' maxima and sums are read by one lane each
 // and reduced in the wave, their weights exp(m - M) kept in LDS, and every thread then folds two
 // neighbouring channels over the splits with independent reads.  The partials' raw halves are read
-// only where a cache has raw positions (a.raw).  8 rows x 6 splits (one layer, 1500 positions): 23 us -> 11
-// us; 512 rows x 4 splits: 36 -> 21 us.
+// only where a cache has raw positions (a.raw).  8 rows x 6 splits (one layer, 1500 positions): 23 -> 8 us;
+// 512 rows x 4 splits: 36 -> 13 us.
 __global__ __launch_bounds__(kAThreads) void att_combine(AttendDev a, GaugeDev G) {
   extern __shared__ float sm[];
   const int d = a.q.d, H = a.kc.H, B = a.q.B, ns = a.nsplit;
@@ -447,6 +475,8 @@ __global__ __launch_bounds__(kAThreads) void att_combine(AttendDev a, GaugeDev G
   const size_t pstride = size_t(2 + 2 * d);
   const float* part = a.part + ((size_t(lv) * B + b) * a.Hq + hq0) * ns * pstride;  // [nj][ns]
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  OutRows out;
+  load_out_rows(out, G, d, lv + a.l0, h);
   for (int jj = w; jj < nj; jj += kAThreads / 64) {
     const float* P = part + size_t(jj) * ns * pstride;
     float M = -INFINITY, L = 0.0f;
@@ -462,22 +492,33 @@ __global__ __launch_bounds__(kAThreads) void att_combine(AttendDev a, GaugeDev G
     if (lane == 0) lsum[jj] = L;
   }
   __syncthreads();
-  const int e2 = a.raw ? d : d / 2;  // channel pairs of a query: gauge-space sums, then raw sums
-  for (int idx = threadIdx.x; idx < nj * e2; idx += kAThreads) {
-    const int jj = idx / e2, e = 2 * (idx - jj * e2);
+  for (int idx = threadIdx.x; idx < nj * (d / 2); idx += kAThreads) {  // channel pairs of a query
+    const int jj = idx / (d / 2), e = 2 * (idx - jj * (d / 2));
     const float* P = part + size_t(jj) * ns * pstride + 2 + e;
     const float* wj = wts + jj * ns;
-    float2 v = make_float2(0.0f, 0.0f);
+    float2 v = make_float2(0.0f, 0.0f), r = v;
+    auto fold = [&](float2& acc, const float* src, float wt) {
+      const float2 p = *reinterpret_cast<const float2*>(src);
+      acc.x = fmaf(p.x, wt, acc.x);
+      acc.y = fmaf(p.y, wt, acc.y);
+    };
+    if (a.raw) {
+#pragma unroll 4
+      for (int sp = 0; sp < ns; ++sp) {
+        fold(v, P + sp * pstride, wj[sp]);
+        fold(r, P + sp * pstride + d, wj[sp]);
+      }
+      *reinterpret_cast<float2*>(maccr + jj * d + e) = r;
+    } else {
 #pragma unroll 8
-    for (int sp = 0; sp < ns; ++sp) {
-      const float2 p = *reinterpret_cast<const float2*>(P + sp * pstride);
-      v.x = fmaf(p.x, wj[sp], v.x);
-      v.y = fmaf(p.y, wj[sp], v.y);
+      for (int sp = 0; sp < ns; ++sp) fold(v, P + sp * pstride, wj[sp]);
     }
-    *reinterpret_cast<float2*>(e < d ? macc + jj * d + e : maccr + jj * d + e - d) = v;
+    *reinterpret_cast<float2*>(macc + jj * d + e) = v;
   }
   __syncthreads();
-  finalize_rows<kJQ>(a, G, macc, a.raw ? maccr : nullptr, lsum, nj, lv, b, h, hq0, wts);
+  const float* raw = a.raw ? maccr : nullptr;
+  if (nj <= 4) finalize_rows<4>(a, G, out, macc, raw, lsum, nj, lv, b, h, hq0, wts);
+  else finalize_rows<kJQ>(a, G, out, macc, raw, lsum, nj, lv, b, h, hq0, wts);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -646,9 +687,11 @@ __device__ __forceinline__ void load_query_rows(QueryRows& q, const GaugeDev& G,
   const int g = G.g, w = threadIdx.x >> 6, m = threadIdx.x & 15, rq = (threadIdx.x >> 4) & 3;
   if (g % 8) return;
   const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  const float invg = 1.0f / float(g);
 #pragma unroll
   for (int p = 0; p < 8; ++p) {
-    const int i = 32 * w + 4 * p + rq, r = i / g, c = 8 * m - r * g;
+    // the row's group: (i + 1/2) / g lies at least 1/256 from an integer
+    const int i = 32 * w + 4 * p + rq, r = int((float(i) + 0.5f) * invg), c = 8 * m - r * g;
     const bool in = c >= 0 && c < g;
     const float4* src = reinterpret_cast<const float4*>(
         G.f32 + gauge_block(l, 0, h, r, G.H, G.R) * g * g + size_t(i - r * g) * g + (in ? c : 0));
@@ -774,14 +817,16 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
   {
     // thread group of kAThreads / (JQ NBLK) lanes per (query, block)
     constexpr int GL = kAThreads / (JQ * NBLK), CPL = NB / GL;
-    static_assert(GL == 32 || GL == 16, "lanes per (query, block)");
+    static_assert((GL == 32 || GL == 16) && CPL % 2 == 0, "lanes per (query, block)");
     const int pr = threadIdx.x / GL, jj = pr / NBLK, k = pr % NBLK, c0 = k * NB + (threadIdx.x % GL) * CPL;
     float acc = 0.0f;
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-      uint32_t hi, lo;
-      split2(qt[jj][c0 + c], hi, lo);
-      acc += bf16_to_f32(hi) + bf16_to_f32(lo);
+    for (int c = 0; c < CPL; c += 2) {
+      const float x0 = qt[jj][c0 + c], x1 = qt[jj][c0 + c + 1];
+      const uint32_t hi = pk_bf16(x0, x1);
+      const float h0 = __uint_as_float(hi << 16), h1 = __uint_as_float(hi & 0xffff0000u);
+      const uint32_t lo = pk_bf16(x0 - h0, x1 - h1);
+      acc += (h0 + __uint_as_float(lo << 16)) + (h1 + __uint_as_float(lo & 0xffff0000u));
     }
 #pragma unroll
     for (int o = 1; o < GL; o <<= 1) acc += __shfl_xor(acc, o);
@@ -793,15 +838,22 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
   bf16x8_t AK[4];
   if constexpr (!KIVI) {
     const int j = n / (2 * NBLK), blk = (n / 2) % NBLK, plane = n & 1;
+    const bool own = 32 * gq / NB == blk;  // the region lies in one block
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      u32x4_t f = {0u, 0u, 0u, 0u};
+      // the fragment's channels as two runs of four: pairs across them, or (8 bits) along them
+      const float* src = &qt[j][32 * gq + frag_chan<BITS>(u, 0)];
+      constexpr int RUN = BITS == 2 || BITS == 3 ? 8 : 4;  // distance of the runs
+      const float4 r0 = *reinterpret_cast<const float4*>(src), r1 = *reinterpret_cast<const float4*>(src + RUN);
+      const float x0[4] = {r0.x, r0.y, r0.z, r0.w}, x1[4] = {r1.x, r1.y, r1.z, r1.w};
+      u32x4_t f;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int ch = 32 * gq + frag_chan<BITS>(u, e);
-        uint32_t hi = 0u, lo = 0u;
-        if (ch / NB == blk) split2(qt[j][ch], hi, lo);
-        f[e >> 1] |= (plane ? lo : hi) << (16 * (e & 1));
+      for (int i = 0; i < 4; ++i) {
+        const float c0 = BITS == 8 ? (i < 2 ? x0[2 * i] : x1[2 * i - 4]) : x0[i];
+        const float c1 = BITS == 8 ? (i < 2 ? x0[2 * i + 1] : x1[2 * i - 3]) : x1[i];
+        const uint32_t hi = pk_bf16(c0, c1);
+        const uint32_t lo = pk_bf16(c0 - __uint_as_float(hi << 16), c1 - __uint_as_float(hi & 0xffff0000u));
+        f[i] = own ? (plane ? lo : hi) : 0u;
       }
       AK[u] = as_bf16x8(f);
     }
@@ -1203,6 +1255,8 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
   }
 
   // 3. per-wave results: maximum and sum per query, gauge-space value sums
+  OutRows out;
+  if (a.nsplit == 1) load_out_rows(out, G, kD, l, h);
   float lsum[NQL];
 #pragma unroll
   for (int qi = 0; qi < NQL; ++qi) lsum[qi] = row16_sum(lp[qi]);
@@ -1276,7 +1330,7 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
     __syncthreads();
   }
   if (a.nsplit == 1) {
-    finalize_rows<JQ>(a, G, &macc[0][0], RAW ? &accr[0][0] : nullptr, mm[1], nj, lv, b, h, hq0, red);
+    finalize_rows<JQ>(a, G, out, &macc[0][0], RAW ? &accr[0][0] : nullptr, mm[1], nj, lv, b, h, hq0, red);
     return;
   }
   const size_t pstride = size_t(2 + 2 * kD);
