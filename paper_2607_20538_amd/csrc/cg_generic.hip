@@ -13,7 +13,8 @@
 // What bounds them: the binary32 matrix cores (256 flops per CU and cycle), then the tile's four
 // dependent phases.  16 layers x 2 x 8 heads x 2048 tokens of 64 channels, g = 64, 4 bits, block 32,
 // bf16: encode 256 -> 74 us, decode 210 -> 66 us per tensor (vector-ALU gauge re-reading G per tile, one
-// thread per block; the matrix-core floor is 27 us, the bytes' 18 us).
+// thread per block; the matrix-core floor is 27 us, the bytes' 18 us); with the three bf16 planes of G
+// (general_planes) encode 44 us.
 #include <algorithm>
 
 #include "cg_internal.h"
@@ -164,8 +165,17 @@ constexpr int general_waves(int kr, int nbw, int store) {
   return store == kStoreRows ? (kr * nbw <= 16 ? 4 : (kr * nbw <= 64 ? 3 : 1)) : 1;
 }
 
-template <int KR, int NBW, int STORE>
+// Whether token rows of bf16 tensors take the three bf16 planes of G (by groups of 4 KR channels): where
+// g is a multiple of 32 and the planes fit a wave's registers.  The other stores keep the binary32 chain
+// (the error-free backend returns z itself, the zfp-style coder follows its last bits).
+constexpr bool general_planes(int kr, int nbw, int store) {
+  return store == kStoreRows && kr > 0 && kr % 8 == 0 && kr * nbw <= 64;
+}
+
+// PL: bf16 tokens stay bf16 in LDS and the gauge runs as three bf16 planes
+template <int KR, int NBW, int STORE, bool PL>
 __global__ __launch_bounds__(kThreads, general_waves(KR, NBW, STORE)) void enc_general(EncArgs a) {
+  static_assert(!PL || general_planes(KR, NBW, STORE), "groups of 32 KK channels");
   extern __shared__ float sm[];
   __shared__ std::conditional_t<STORE == kStoreOther, ZfpTables, char> ztab;
   const ViewDev& X = a.X;
@@ -178,7 +188,9 @@ __global__ __launch_bounds__(kThreads, general_waves(KR, NBW, STORE)) void enc_g
   const int rows16 = (TT + 15) & ~15;
   const int n = kivi ? c.kvc : c.n, row_bytes = d * c.bits / 8;
   float* xs = sm;
-  float* zs = xs + rows16 * dp;
+  uint8_t* xb = reinterpret_cast<uint8_t*>(sm);
+  const int xpitch = bf16_pitch(d);
+  float* zs = PL ? reinterpret_cast<float*>(xb + rows16 * xpitch) : xs + rows16 * dp;
   float2* red = reinterpret_cast<float2*>(zs + rows16 * dp);
   uint8_t* cst = reinterpret_cast<uint8_t*>(red + (tiles ? TT * (d / n) : 0));
   const int sv = blockIdx.y;
@@ -189,8 +201,10 @@ __global__ __launch_bounds__(kThreads, general_waves(KR, NBW, STORE)) void enc_g
   const size_t xbase = size_t(lv) * X.sl + size_t(b) * X.sb + size_t(h) * X.sh;
 
   GaugeRaw<(KR > 0 ? KR : 4), NBW> graw;
+  GaugePlanes<(PL ? KR / 8 : 1), NBW> gp;
   const WaveTile wt = wave_tile<NBW>(d);
-  if constexpr (KR > 0) load_gauge_rows<KR, NBW>(graw, a.G, l, s, h, wt);
+  if constexpr (PL) load_gauge_planes<KR / 8, NBW>(gp, a.G, l, s, h, wt);
+  else if constexpr (KR > 0) load_gauge_rows<KR, NBW>(graw, a.G, l, s, h, wt);
   if constexpr (STORE == kStoreOther) {
     if (c.backend == CG_BACKEND_ZFP) zfp_tables_init(ztab);  // read after the barriers below
   }
@@ -209,7 +223,7 @@ __global__ __launch_bounds__(kThreads, general_waves(KR, NBW, STORE)) void enc_g
     size_t off[kAhead];
 #pragma unroll
     for (int i = 0; i < kAhead; ++i) off[i] = xbase + size_t(min(tile * TT + gt[i], X.T - 1)) * X.st + 8 * gc[i];
-    if (X.bf16) {
+    if (PL || X.bf16) {
 #pragma unroll
       for (int i = 0; i < kAhead; ++i)
         if (i * kThreads < TT * d8) xr[i] = load_raw8<true>(X.ptr, off[i]);
@@ -222,7 +236,7 @@ __global__ __launch_bounds__(kThreads, general_waves(KR, NBW, STORE)) void enc_g
   auto raw_tile = [&](int tile) { return kivi && tile * TT >= a.tq; };  // KIVI window rows: no gauge
   if (ahead && !raw_tile(tb)) fetch(tb);
   float A[NBW][KR > 0 ? KR : 1];
-  if constexpr (KR > 0) gauge_operand<KR, NBW>(graw, A);
+  if constexpr (KR > 0 && !PL) gauge_operand<KR, NBW>(graw, A);
   int flags = 0;
   for (int tile = tb; tile < te; ++tile) {
     const int tile0 = tile * TT, ntok = min(TT, X.T - tile0);
@@ -249,6 +263,16 @@ __global__ __launch_bounds__(kThreads, general_waves(KR, NBW, STORE)) void enc_g
     }
     if (nq == 0) continue;
     auto stage = [&](int t, int c8, const Raw8& r) {
+      if constexpr (PL) {
+        const uint32_t w[4] = {r.v[0].x, r.v[0].y, r.v[0].z, r.v[0].w};
+        if (t < nq && !skip) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if ((w[e] & 0x7f80u) == 0x7f80u || (w[e] & 0x7f800000u) == 0x7f800000u) flags |= CG_FLAG_NONFINITE;
+        }
+        *reinterpret_cast<uint4*>(xb + t * xpitch + 16 * c8) = r.v[0];
+        return;
+      }
       float x[8];
       raw8_values(r, X.bf16, x);
       if (t < nq && !skip) {  // staged rows: checked when quantised
@@ -267,12 +291,13 @@ __global__ __launch_bounds__(kThreads, general_waves(KR, NBW, STORE)) void enc_g
       for (int idx = tid; idx < TT * d8; idx += kThreads) {
         const int t = small_div(idx, inv8), c8 = idx - t * d8;
         const size_t off = xbase + size_t(min(tile0 + t, X.T - 1)) * X.st + 8 * c8;
-        stage(t, c8, X.bf16 ? load_raw8<true>(X.ptr, off) : load_raw8<false>(X.ptr, off));
+        stage(t, c8, PL || X.bf16 ? load_raw8<true>(X.ptr, off) : load_raw8<false>(X.ptr, off));
       }
     }
     __syncthreads();
     if (ahead && tile + 1 < te && !raw_tile(tile + 1)) fetch(tile + 1);
-    if constexpr (KR > 0) gauge_mfma<KR, NBW>(A, xs, zs, (ntok + 15) / 16, dp, wt);
+    if constexpr (PL) gauge_planes_mfma<KR / 8, NBW>(gp, xb, zs, (ntok + 15) / 16, d, dp, wt);
+    else if constexpr (KR > 0) gauge_mfma<KR, NBW>(A, xs, zs, (ntok + 15) / 16, dp, wt);
     else gauge_tile(xs, zs, ntok, d, dp, a.G, l, s, h);
     __syncthreads();
     if (skip) continue;
@@ -564,7 +589,8 @@ hipError_t launch_encode_generic(int s, const ViewDev& X, int l0, const GaugeDev
   a.TT = tile_tokens(c, d, pt.pages != nullptr, X.T, nslices);
   a.tiles_per_wg = tiles_per_wg((X.T + a.TT - 1) / a.TT, nslices);
   const int rows16 = (a.TT + 15) & ~15;
-  size_t smem = size_t(2) * rows16 * (d + kPad) * sizeof(float);
+  const size_t tile_f32 = size_t(rows16) * (d + kPad) * sizeof(float);
+  size_t smem = tile_f32;  // zs, codes and ranges
   if (c.backend == CG_BACKEND_BLOCK_UNIFORM || (c.backend == CG_BACKEND_KIVI && s == 1)) {
     smem += size_t(a.TT) * (d * c.bits / 8);
     if (c.backend == CG_BACKEND_BLOCK_UNIFORM && c.bt > 1) smem += size_t(a.TT) * (d / c.n) * sizeof(float2);
@@ -575,11 +601,19 @@ hipError_t launch_encode_generic(int s, const ViewDev& X, int l0, const GaugeDev
   const dim3 grid(((X.T + a.TT - 1) / a.TT + a.tiles_per_wg - 1) / a.tiles_per_wg, nslices);
   return by_gauge(G.g, d, [&](auto kr, auto nbw) {
     constexpr int KR = decltype(kr)::value, NBW = decltype(nbw)::value;
-    const void* fn = by_rows ? (const void*)enc_general<KR, NBW, kStoreRows> : (const void*)enc_general<KR, NBW, kStoreOther>;
-    hipError_t e = set_smem(fn, smem + sizeof(ZfpTables));
+    const void* fn = by_rows ? (const void*)enc_general<KR, NBW, kStoreRows, false>
+                             : (const void*)enc_general<KR, NBW, kStoreOther, false>;
+    size_t bytes = smem + tile_f32;  // and the binary32 tokens
+    if constexpr (general_planes(KR, NBW, kStoreRows)) {
+      if (by_rows && X.bf16) {
+        fn = (const void*)enc_general<KR, NBW, kStoreRows, true>;
+        bytes = smem + size_t(rows16) * bf16_pitch(d);
+      }
+    }
+    hipError_t e = set_smem(fn, bytes + sizeof(ZfpTables));
     if (e != hipSuccess) return e;
     void* args[] = {&a};
-    return hipLaunchKernel(fn, grid, dim3(kThreads), args, smem, st);
+    return hipLaunchKernel(fn, grid, dim3(kThreads), args, bytes, st);
   });
 }
 
