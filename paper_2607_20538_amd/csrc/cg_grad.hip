@@ -17,8 +17,8 @@
 // in binary32, W, U, dL/dU and dL/dW in binary64 (the binary32 products accumulate exactly),
 // and accumulates its part of dL/dM in binary64 registers (a (d/16) x (d/16) tile per thread),
 // written as one partial per workgroup; grad_data_mfma does the same for d = 128 with 16-token
-// blocks on the binary64 matrix cores; grad_reduce sums the partials in a fixed order
-// (deterministic); grad_frechet forms dL/dG and the Frechet adjoint per gauge block in binary64
+// blocks on the binary64 matrix cores, and grad_groups, for groups of at most 32 channels, forms
+// partials of dL/dG itself; grad_reduce sums the partials in a fixed order (deterministic); grad_frechet forms dL/dG and the Frechet adjoint per gauge block in binary64
 // (power series of the scaled block matrix by the Paterson-Stockmeyer scheme, then squaring),
 // and grad_frechet16 does the same for groups of at most 16 channels in one wave, in LDS.
 // Binary64 through the data pass matters: dL/dA is the antisymmetric part of dL/dS, which for
@@ -97,7 +97,7 @@ struct GradArgs {
   ViewDev X;
   const float* M;        // [L][H][d][d]
   const double* stats;   // [L][4] from the forward statistics
-  double* part;          // [L][H][B * chunks][d][d] partial dL/dM
+  double* part;          // [L][H][B * chunks][d][d] partial dL/dM, or [d][g] partial dL/dG
   int Tb, nblk, chunks, blocks_per_wg;
   float inv_tau, tau, lam_f, lam_r;
   double inv_count;      // 1 / (coefficients per layer)
@@ -323,10 +323,144 @@ __global__ __launch_bounds__(kDataThreads) void grad_data_mfma(GradArgs a) {
     for (int v = 0; v < 4; ++v) out[size_t(n0 + 4 * v + mk) * d + 16 * jt + mi] = acc[jt][v];
 }
 
-// dL/dM per (layer, head): the partials summed in order, binary64
-__global__ __launch_bounds__(256) void grad_reduce(const double* part, int nparts, int d, double* dM) {
+// The data pass for d = 128, Tb = 16 and groups of at most 32 channels.  With the token transform
+// first, Xt = C_Tb X, a block is U = Xt M^T and its derivatives are dL/dZ = dL/dU C_d and, per group,
+// dL/dG = (dL/dZ)^T Xt (Z = Xt G^T), so dL/dM is never formed: a partial holds d x g entries instead of
+// d x d, and the product with X runs over the group's g channels instead of 128.  dL/dZ uses the cosines'
+// symmetry, C_d[v][127 - c] = (-1)^v C_d[v][c]: the even and the odd frequencies each give 64 channels,
+// whose sum and difference are the mirrored pair, half the products.  U itself keeps the dense M as
+// grad_prep rounds it: coefficients at the kink of |U| take their sign from it.  Everything runs on the
+// binary64 matrix cores, transposed so that a wave's results are rows of the next product's right
+// operand; Xt^T, dL/dU^T and the two halves of dL/dZ^T cross the waves through LDS ([row][token
+// frequency], rows padded to 18 doubles), one barrier each, Xt^T in two buffers since dL/dG of a block
+// still reads it while the next one is written.  Wave w takes channels [16 w, + 16) of Xt and dL/dG,
+// frequencies 2 (16 (w / 2) + i) + w % 2 of U and channels [16 (w / 2), + 16) of its parity's dL/dZ.
+// 56 (g = 32: 60) steps of 64 matrix-core cycles per wave and block against 72 with dL/dM, 191 us of
+// matrix cores for 8 x 8 heads of 4096 tokens.  M's fragments stay binary32 and are converted at use, which
+// leaves room for two workgroups a CU.  Those 8 x 8 heads, g = 16: 271 us (346 by grad_data_mfma), and the sum
+// of the partials 4.7 us (21), the Frechet step 12 us (43, it formed dL/dG from dL/dM).
+constexpr int kGrpP = 18;
+template <bool BF16, int KT>  // KT: 16-channel tiles a wave's groups span (g <= 16: 1, g = 32: 2)
+__global__ __launch_bounds__(kDataThreads, 4) void grad_groups(GradArgs a, int g) {
+  constexpr int d = 128, Tb = 16;
+  extern __shared__ double smd3[];
+  double* xs = smd3;                // Xt^T [2][d][kGrpP]
+  double* us = xs + 2 * d * kGrpP;  // dL/dU^T [parity][64][kGrpP]
+  double* ps = us + d * kGrpP;      // halves of dL/dZ^T [parity][64][kGrpP]
+  double* tab = ps;                 // cosine table (before the first block)
+  const ViewDev& X = a.X;
+  const int wg = blockIdx.x, chunk = wg % a.chunks, sl = wg / a.chunks;
+  const int h = sl % X.H, b = (sl / X.H) % X.B, l = sl / (X.H * X.B);
+  const int tid = int(threadIdx.x), lane = tid & 63, mi = lane & 15, mk = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), par = w & 1, q0 = 16 * (w >> 1);
+  const int k0 = chunk * a.blocks_per_wg, k1 = min(a.nblk, k0 + a.blocks_per_wg);
+  const int jb = KT == 2 ? 16 * (w & ~1) : 16 * w;  // first channel of the wave's groups
+
+  // M[v of row mi][4 st + mk]
+  const float* Mg = a.M + ((size_t(l) * X.H + h) * d + 2 * (q0 + mi) + par) * d + mk;
+  float mf[32];
+#pragma unroll
+  for (int st = 0; st < 32; ++st) mf[st] = Mg[4 * st];
+  // X[4 st + mk][16 w + mi] of a block, raw until used
+  typedef std::conditional_t<BF16, uint16_t, float> xt;
+  const xt* xp = static_cast<const xt*>(X.ptr) + size_t(l) * X.sl + size_t(b) * X.sb + size_t(h) * X.sh +
+                 size_t(k0 * Tb + mk) * X.st + 16 * w + mi;
+  xt rx[4];
+  auto fetch = [&]() {
+#pragma unroll
+    for (int st = 0; st < 4; ++st) rx[st] = xp[size_t(4 * st) * X.st];
+    xp += size_t(Tb) * X.st;
+  };
+  if (k0 < k1) fetch();
+  dct_table(tab, d);
+  double cu[4];  // C_Tb[mi][4 st + mk]
+#pragma unroll
+  for (int st = 0; st < 4; ++st)
+    cu[st] = (mi == 0 ? sqrt(1.0 / Tb) : sqrt(2.0 / Tb)) * tab[(2 * (4 * st + mk) + 1) * mi * (d / Tb) % (4 * d)];
+  double cb[16];  // C_d[2 (4 st + mk) + par][q0 + mi]
+#pragma unroll
+  for (int st = 0; st < 16; ++st) {
+    const int v = 2 * (4 * st + mk) + par;
+    cb[st] = (v == 0 ? sqrt(1.0 / d) : sqrt(2.0 / d)) * tab[(2 * (q0 + mi) + 1) * v % (4 * d)];
+  }
+  const double lf = a.stats[4 * l + 0], D = a.stats[4 * l + 3] + 1e-12;
+  const double cr = a.lam_r * a.inv_count, tau = a.tau;
+  double rw[4];  // 2 lambda_f (rho(mi, v) - L_freq) / D of the lane's four frequencies
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const double fu = double(mi) / (Tb - 1), fv = double(2 * (q0 + 4 * v + mk) + par) / (d - 1);
+    rw[v] = 2.0 * a.lam_f / D * (sqrt(fu * fu + fv * fv) * 0.70710678118654752 - lf);
+  }
+  f64x4_t acc[KT];
+#pragma unroll
+  for (int q = 0; q < KT; ++q) acc[q] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+  for (int blk = k0; blk < k1; ++blk, xs = xs == smd3 ? smd3 + d * kGrpP : smd3) {
+    // Xt^T, channels 16 w .. + 15
+    f64x4_t xd = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int st = 0; st < 4; ++st) {
+      float v;
+      if constexpr (BF16) v = bf16_to_f32(rx[st]);
+      else v = rx[st];
+      xd = __builtin_amdgcn_mfma_f64_16x16x4f64(double(v), cu[st], xd, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) xs[(16 * w + 4 * v + mk) * kGrpP + mi] = xd[v];
+    __syncthreads();  // also: the cosine table is read, dL/dZ of the previous block too
+    if (blk + 1 < k1) fetch();
+    // U^T (frequency x token frequency)
+    f64x4_t ud = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int st = 0; st < 32; ++st) asm volatile("" : "+v"(mf[st]));  // kept binary32: converted per use
+#pragma unroll
+    for (int st = 0; st < 32; ++st)
+      ud = __builtin_amdgcn_mfma_f64_16x16x4f64(double(mf[st]), xs[(4 * st + mk) * kGrpP + mi], ud, 0, 0, 0);
+    // dL/dU = U rw + lambda_r sign(U) / (N (tau + |U|)), the reciprocal as in grad_data_mfma
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const double U = ud[v], q = tau + fabs(U);
+      double r = __builtin_amdgcn_rcp(q);
+      r = fma(r, fma(-q, r, 1.0), r);
+      r = fma(r, fma(-q, r, 1.0), r);
+      const double sg = U > 0.0 ? cr : (U < 0.0 ? -cr : 0.0);
+      us[(64 * par + q0 + 4 * v + mk) * kGrpP + mi] = fma(U, rw[v], sg * r);
+    }
+    __syncthreads();
+    // this parity's part of dL/dZ^T, channels q0 .. q0 + 15
+    f64x4_t pq = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int st = 0; st < 16; ++st)
+      pq = __builtin_amdgcn_mfma_f64_16x16x4f64(cb[st], us[(64 * par + 4 * st + mk) * kGrpP + mi], pq, 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) ps[(64 * par + q0 + 4 * v + mk) * kGrpP + mi] = pq[v];
+    __syncthreads();
+    // dL/dG rows 16 w .. + 15 += dL/dZ^T Xt: channel c < 64 is the sum of the parities' parts, 127 - c
+    // their difference
+    const int c = w < 4 ? 16 * w + mi : d - 1 - (16 * w + mi);
+#pragma unroll
+    for (int st = 0; st < 4; ++st) {
+      const double ev = ps[c * kGrpP + 4 * st + mk], od = ps[(64 + c) * kGrpP + 4 * st + mk];
+      const double gz = w < 4 ? ev + od : ev - od;
+#pragma unroll
+      for (int q = 0; q < KT; ++q)
+        acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(gz, xs[(jb + 16 * q + mi) * kGrpP + 4 * st + mk], acc[q], 0, 0, 0);
+    }
+  }
+  // partial [d][g]: row i, column j of i's group
+  double* out = a.part + ((size_t(l) * X.H + h) * (size_t(X.B) * a.chunks) + size_t(b) * a.chunks + chunk) * d * g;
+#pragma unroll
+  for (int q = 0; q < KT; ++q)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = 16 * w + 4 * v + mk, j = jb + 16 * q + mi;
+      if (i / g == j / g) out[i * g + j % g] = acc[q][v];
+    }
+}
+
+// dL/dM (or dL/dG) per (layer, head): the n-entry partials summed in order, binary64
+__global__ __launch_bounds__(256) void grad_reduce(const double* part, int nparts, int n, double* dM) {
   const int lh = blockIdx.y;
-  const size_t dd = size_t(d) * d;
+  const size_t dd = size_t(n);
   for (size_t idx = blockIdx.x * size_t(blockDim.x) + threadIdx.x; idx < dd; idx += size_t(gridDim.x) * blockDim.x) {
     double acc = 0.0;
     for (int p = 0; p < nparts; ++p) acc += part[(size_t(lh) * nparts + p) * dd + idx];
@@ -567,8 +701,8 @@ __device__ double wg_norm1(const double* Mx, int g, double* red) {
 // One workgroup per gauge block (l, h, r): dL/dG from dL/dM, then the Frechet adjoint and
 // dL/dA.  work: twelve g x g binary64 matrices per block.
 template <int MODE>
-__global__ __launch_bounds__(frechet_threads<MODE>()) void grad_frechet(const double* dM, const float* A, int s, int H, int R, int g,
-                                                             int d, double* work, double* grad) {
+__global__ __launch_bounds__(frechet_threads<MODE>()) void grad_frechet(const double* dM, const double* dG, const float* A, int s,
+                                                             int H, int R, int g, int d, double* work, double* grad) {
   constexpr int NT = frechet_threads<MODE>();
   __shared__ double red[NT];
   __shared__ double tab[4 * kMaxD];
@@ -594,7 +728,13 @@ __global__ __launch_bounds__(frechet_threads<MODE>()) void grad_frechet(const do
   const float* Ab = A + ((((size_t(l) * 2 + s) * H + h) * R + r) * gg);
   // dL/dG = C_d^T dL/dM on the block (entry (c, k) sums over v in order) and S^T = A^T - A
   constexpr int QW = 16;  // most outputs per thread on the shared-load path (g^2 / NT: 16 at g = 128 and 64)
-  if (MODE == kFrechet128 && g == d) {
+  if (MODE == kFrechetSmall && dG) {  // formed by the data pass
+    for (int idx = int(threadIdx.x); idx < int(gg); idx += NT) {
+      const int c = idx / g, k = idx - c * g;
+      Es[idx] = dG[(size_t(lh) * d + r * g + c) * g + k];
+      Mm[idx] = double(Ab[size_t(k) * g + c]) - double(Ab[idx]);
+    }
+  } else if (MODE == kFrechet128 && g == d) {
     // one group per head: dL/dG = C_d^T dL/dM as one product, C_d^T staged in T1 from the table
     for (int idx = int(threadIdx.x); idx < int(gg); idx += NT) {
       const int c = idx / g, v = idx - c * g;
@@ -735,11 +875,11 @@ __global__ __launch_bounds__(frechet_threads<MODE>()) void grad_frechet(const do
 // and the g x g part follows grad_frechet step for step (norms, scaling, series, squarings),
 // without the global work area or the workgroup-wide tiles a 16 x 16 product does not fill.
 constexpr int kF16 = 16, kF16P = 17;
-__global__ __launch_bounds__(64) void grad_frechet16(const double* dM, const float* A, int s, int H, int R, int g, int d,
-                                                     double* grad) {
+__global__ __launch_bounds__(64) void grad_frechet16(const double* dM, const double* dG, const float* A, int s, int H,
+                                                     int R, int g, int d, double* grad) {
   __shared__ double tab[4 * kMaxD];
   __shared__ double mt[12][kF16 * kF16P];
-  dct_table(tab, d);
+  if (!dG) dct_table(tab, d);
   const int lane = int(threadIdx.x), mi = lane & 15, mk = lane >> 4;
   const int blk = blockIdx.x, r = blk % R, lh = blk / R, h = lh % H, l = lh / H;
   const int gg = g * g;
@@ -752,7 +892,15 @@ __global__ __launch_bounds__(64) void grad_frechet16(const double* dM, const flo
   // dL/dG = C_d^T dL/dM on the block and S^T = A^T - A, zero outside g x g: lane holds column
   // k = lane % 16 of rows c = lane / 16 + 4 q, so one load of dL/dM[v][r g + k] serves its four
   // entries (each summed over v in order)
-  {
+  if (dG) {  // formed by the data pass
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = lane & 15, c = (lane >> 4) + 4 * q;
+      const bool in = k < g && c < g;
+      Es[at(c, k)] = in ? dG[(size_t(lh) * d + r * g + c) * g + k] : 0.0;
+      Mm[at(c, k)] = in ? double(Ab[k * g + c]) - double(Ab[c * g + k]) : 0.0;
+    }
+  } else {
     const int k = lane & 15, c0 = lane >> 4;
     const bool kin = k < g;
     double acc[4];
@@ -923,6 +1071,10 @@ hipError_t launch_gauge_grad(int s, const ViewDev& X, const GaugeDev& G, const f
   double* dM = reinterpret_cast<double*>(base + lay.off_dm);
   double* work = reinterpret_cast<double*>(base + lay.off_work);
   const int d = X.d, R = d / G.g, nblk = X.T / Tb;
+  // Groups of at most 32 channels take the pass that forms dL/dG itself: 271 us at g = 16 and 293 at g = 32
+  // for 8 x 8 heads of 4096 tokens, against 346 through dL/dM.  A group of 64 would need 68 matrix-core steps
+  // of the dense pass's 72 and hold twice the accumulators, so it stays there.
+  const bool groups = d == 128 && Tb == 16 && G.g <= 32 && !force_generic;
   hipLaunchKernelGGL(grad_prep, dim3((d * (d / kPrepRows) + 255) / 256, X.L * X.H), dim3(256), 0, st, s, G, X.H, d, M);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   GradArgs a{};
@@ -934,16 +1086,40 @@ hipError_t launch_gauge_grad(int s, const ViewDev& X, const GaugeDev& G, const f
   a.nblk = nblk;
   a.chunks = lay.chunks;
   a.blocks_per_wg = lay.blocks_per_wg;
+  if (groups) {
+    // Two workgroups a CU are resident, 512 on the chip, and each sets up its fragments for about two
+    // blocks' time: the split (never more chunks than the workspace holds) whose waves of workgroups end first.
+    const int64_t sl = int64_t(X.L) * X.B * X.H;
+    int64_t best = 0;
+    for (int ch = 1; ch <= lay.chunks; ++ch) {
+      const int bpw = (nblk + ch - 1) / ch;
+      const int64_t cost = (sl * ch + 511) / 512 * (bpw + 2);
+      if (ch == 1 || cost < best) {
+        best = cost;
+        a.blocks_per_wg = std::max(bpw, 1);
+      }
+    }
+    a.chunks = nblk > 0 ? (nblk + a.blocks_per_wg - 1) / a.blocks_per_wg : 1;
+  }
   a.tau = tau;
   a.inv_tau = 1.0f / tau;
   a.lam_f = lam_f;
   a.lam_r = lam_r;
   const double count = double(X.B) * X.H * nblk * Tb * d;
   a.inv_count = count > 0 ? 1.0 / count : 0.0;
-  const int nwg = X.L * X.B * X.H * lay.chunks;
+  const int nwg = X.L * X.B * X.H * a.chunks;
   const size_t smem = size_t(2) * Tb * (d + 1) * sizeof(double) +
                       (size_t(d) * (d + 1) + size_t(Tb) * (d + 1) + size_t(Tb) * Tb) * sizeof(float);
-  if (nblk > 0 && d == 128 && Tb == 16 && !force_generic) {
+  if (nblk > 0 && groups) {
+    const size_t smg = size_t(4) * 128 * kGrpP * sizeof(double);
+    const void* fn = G.g <= 16 ? (X.bf16 ? (const void*)grad_groups<true, 1> : (const void*)grad_groups<false, 1>)
+                               : (X.bf16 ? (const void*)grad_groups<true, 2> : (const void*)grad_groups<false, 2>);
+    if ((e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smg)) != hipSuccess) return e;
+    int g = G.g;
+    void* args[] = {&a, &g};
+    if ((e = hipLaunchKernel(fn, dim3(nwg), dim3(kDataThreads), args, smg, st)) != hipSuccess) return e;
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  } else if (nblk > 0 && d == 128 && Tb == 16 && !force_generic) {
     const size_t smf = (size_t(16) * 130 + size_t(16) * 128) * sizeof(double);
     const void* fn = X.bf16 ? (const void*)grad_data_mfma<true> : (const void*)grad_data_mfma<false>;
     if ((e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smf)) != hipSuccess) return e;
@@ -964,19 +1140,21 @@ hipError_t launch_gauge_grad(int s, const ViewDev& X, const GaugeDev& G, const f
     }
     if (e != hipSuccess) return e;
   }
-  const int nparts = nblk > 0 ? X.B * lay.chunks : 0;
-  hipLaunchKernelGGL(grad_reduce, dim3((d * d + 255) / 256, X.L * X.H), dim3(256), 0, st, part, nparts, d, dM);
+  const int nparts = nblk > 0 ? X.B * a.chunks : 0;
+  const int n = d * (groups ? G.g : d);  // entries of a partial: dL/dG's groups, or dL/dM
+  const double* dG = groups ? dM : nullptr;
+  hipLaunchKernelGGL(grad_reduce, dim3((n + 255) / 256, X.L * X.H), dim3(256), 0, st, part, nparts, n, dM);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (G.g == 128)
-    hipLaunchKernelGGL(grad_frechet<kFrechet128>, dim3(X.L * X.H * R), dim3(kWideThreads), 0, st, dM, A, s, X.H, R, G.g,
+    hipLaunchKernelGGL(grad_frechet<kFrechet128>, dim3(X.L * X.H * R), dim3(kWideThreads), 0, st, dM, dG, A, s, X.H, R, G.g,
                        d, work, grad);
   else if (G.g <= kF16)
-    hipLaunchKernelGGL(grad_frechet16, dim3(X.L * X.H * R), dim3(64), 0, st, dM, A, s, X.H, R, G.g, d, grad);
+    hipLaunchKernelGGL(grad_frechet16, dim3(X.L * X.H * R), dim3(64), 0, st, dM, dG, A, s, X.H, R, G.g, d, grad);
   else if (G.g % 64 == 0)
-    hipLaunchKernelGGL(grad_frechet<kFrechet64>, dim3(X.L * X.H * R), dim3(kGradThreads), 0, st, dM, A, s, X.H, R, G.g,
+    hipLaunchKernelGGL(grad_frechet<kFrechet64>, dim3(X.L * X.H * R), dim3(kGradThreads), 0, st, dM, dG, A, s, X.H, R, G.g,
                        d, work, grad);
   else
-    hipLaunchKernelGGL(grad_frechet<kFrechetSmall>, dim3(X.L * X.H * R), dim3(kGradThreads), 0, st, dM, A, s, X.H, R,
+    hipLaunchKernelGGL(grad_frechet<kFrechetSmall>, dim3(X.L * X.H * R), dim3(kGradThreads), 0, st, dM, dG, A, s, X.H, R,
                        G.g, d, work, grad);
   return hipGetLastError();
 }

@@ -161,3 +161,25 @@ def test_descent_steps_lower_the_objective():
     for idx in np.ndindex(*G.shape[:-2]):
         Gb = G[idx].astype(np.float64)
         assert np.abs(Gb.T @ Gb - eye).max() < 1e-5
+
+
+@pytest.mark.parametrize("g", [1, 4, 8, 16, 32])
+@pytest.mark.parametrize("shape", [(1, 1, 1, 16), (2, 2, 3, 233)], ids=["one_block", "ragged"])
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+def test_group_data_pass(g, shape, dt):
+    """d = 128, 16-token blocks and groups of at most 32 channels: the data pass that forms dL/dG per
+    group, at every group width, with one block and with several per workgroup and a token tail.  The
+    criterion is the module's: M keeps its binary32 rounding, everything after it is binary64."""
+    L_, B, H, T = shape
+    d = 128
+    rng = np.random.default_rng(31 * g + T)
+    X = (rng.standard_normal((L_, B, H, T, d)) * rng.uniform(0.5, 3.0, size=(1, 1, 1, 1, d))).astype(np.float32)
+    if dt == "bf16":
+        X = synth.round_bf16_bits(X)
+    A = (0.3 * rng.standard_normal((L_, 2, H, d // g, g, g))).astype(np.float32)
+    for s in (0, 1):
+        grad, stats, sref = _run(X, A, s, g, 16)
+        ref = O.spectral_train_grad(X, A.astype(np.float64), s, Tb=16)
+        assert np.abs(grad - ref).max() <= TOL * np.abs(ref).max(), (g, shape, dt, s)
+        np.testing.assert_array_equal(grad, -np.swapaxes(grad, -1, -2))
+        np.testing.assert_allclose(stats, sref, rtol=1e-12)
