@@ -1180,7 +1180,7 @@ __global__ __launch_bounds__(kThreads, OUT_BF16 ? 3 : 2) void dec_keys(MfmaArgs 
 //     most 2^-16 of the group's norm and typically by 2^-16 / sqrt(3 g) of it (independent
 //     rounding errors), against the bf16 criterion of one ulp plus 1e-5 of the group's norm.
 template <int KS, int RATE, bool OUT_BF16>
-__global__ __launch_bounds__(kThreads, 2) void dec_zfp(MfmaArgs a) {
+__global__ __launch_bounds__(kThreads, KS == 8 && RATE > 4 ? 3 : 4) void dec_zfp(MfmaArgs a) {
   constexpr int YB = OUT_BF16 ? 2 : 4;
   constexpr int NPL = OUT_BF16 ? 2 : 3;  // planes of zhat
   __shared__ __attribute__((aligned(16))) uint8_t zpl[NPL][kTok * kRowBytes];
@@ -1210,13 +1210,21 @@ __global__ __launch_bounds__(kThreads, 2) void dec_zfp(MfmaArgs a) {
 
   const int tid = int(threadIdx.x), u = tid >> 5, cb = tid & 31;
   zfp_tables_init(ztab);
+  // the next tile's block, loaded while this one is decoded and multiplied
+  uint32_t wn[4] = {};
+  auto fetch = [&](int t) {
+    if (4 * u < a.T - t * kTok) {
+      const size_t blk = (cslice * size_t(a.T_cap / 4) + (a.t0 + t * kTok) / 4 + u) * (kD / 4) + cb;
+      zfp_load<RATE>(a.codes + blk * (2 * RATE), wn);
+    }
+  };
+  fetch(tb);
   __syncthreads();
   for (int t = tb; t < te; ++t) {
     // 1. blocks -> zhat planes (the view's token count and offset are multiples of 4)
     if (4 * u < a.T - t * kTok) {
-      const size_t blk = (cslice * size_t(a.T_cap / 4) + (a.t0 + t * kTok) / 4 + u) * (kD / 4) + cb;
-      uint32_t wd[4];
-      zfp_load<RATE>(a.codes + blk * (2 * RATE), wd);
+      const uint32_t wd[4] = {wn[0], wn[1], wn[2], wn[3]};
+      if (t + 1 < te) fetch(t + 1);
       float v[16];
       zfp_decode_block<RATE>(wd, ztab, v);
 #pragma unroll

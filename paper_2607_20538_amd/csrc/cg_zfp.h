@@ -43,7 +43,12 @@ namespace {
 // ------------------------------------------------------------------------------------------
 __host__ __device__ __forceinline__ int32_t wadd(int32_t a, int32_t b) { return int32_t(uint32_t(a) + uint32_t(b)); }
 __host__ __device__ __forceinline__ int32_t wsub(int32_t a, int32_t b) { return int32_t(uint32_t(a) - uint32_t(b)); }
-__host__ __device__ __forceinline__ int32_t wdbl(int32_t a) { return int32_t(uint32_t(a) << 1); }
+// (x + y, y - x) in place
+__host__ __device__ __forceinline__ void wsumdiff(int32_t& x, int32_t& y) {
+  const int32_t t = x;
+  x = wadd(t, y);
+  y = wsub(y, t);
+}
 
 // 1/16 [[4 4 4 4] [5 1 -1 -5] [-4 4 4 -4] [-2 6 -6 2]] applied to (a, b, c, e) by lifting
 __host__ __device__ __forceinline__ void zfp_fwd4(int32_t& a, int32_t& b, int32_t& c, int32_t& e) {
@@ -55,10 +60,10 @@ __host__ __device__ __forceinline__ void zfp_fwd4(int32_t& a, int32_t& b, int32_
 }
 __host__ __device__ __forceinline__ void zfp_inv4(int32_t& a, int32_t& b, int32_t& c, int32_t& e) {
   b = wadd(b, e >> 1); e = wsub(e, b >> 1);
-  b = wadd(b, e); e = wsub(wdbl(e), b);
-  c = wadd(c, a); a = wsub(wdbl(a), c);
-  b = wadd(b, c); c = wsub(wdbl(c), b);
-  e = wadd(e, a); a = wsub(wdbl(a), e);
+  wsumdiff(b, e);
+  wsumdiff(c, a);
+  wsumdiff(b, c);
+  wsumdiff(e, a);
 }
 
 // sequency position k -> block entry 4 j + i (by i + j, then i^2 + j^2, then j)
@@ -103,56 +108,63 @@ __host__ __device__ __forceinline__ void transpose8(uint32_t& lo, uint32_t& hi) 
   lo = l2;
 }
 
-// bytes (a.b0, b.b0, a.b1, b.b1) and (a.b2, b.b2, a.b3, b.b3) of two words
-__host__ __device__ __forceinline__ uint32_t interleave_lo(uint32_t a, uint32_t b) {
-  return (a & 0xFFu) | ((b & 0xFFu) << 8) | ((a & 0xFF00u) << 8) | ((b & 0xFF00u) << 16);
+// four bytes of (hi, lo) by selector: byte i of the result is byte (sel >> 8 i) & 7 of lo (0..3), hi (4..7)
+template <uint32_t SEL>
+__host__ __device__ __forceinline__ uint32_t byte_perm(uint32_t hi, uint32_t lo) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_perm(hi, lo, SEL);
+#else
+  const uint64_t v = (uint64_t(hi) << 32) | lo;
+  uint32_t r = 0u;
+  for (int i = 0; i < 4; ++i) r |= (uint32_t(v >> (8 * ((SEL >> (8 * i)) & 7u))) & 0xFFu) << (8 * i);
+  return r;
+#endif
 }
-__host__ __device__ __forceinline__ uint32_t interleave_hi(uint32_t a, uint32_t b) {
-  return ((a >> 16) & 0xFFu) | ((b >> 8) & 0xFF00u) | ((a >> 8) & 0xFF0000u) | (b & 0xFF000000u);
-}
-// even bytes (w0.b0, w0.b2, w1.b0, w1.b2) and odd bytes (w0.b1, w0.b3, w1.b1, w1.b3)
-__host__ __device__ __forceinline__ uint32_t even_bytes(uint32_t w0, uint32_t w1) {
-  return (w0 & 0xFFu) | ((w0 >> 8) & 0xFF00u) | ((w1 & 0xFFu) << 16) | ((w1 << 8) & 0xFF000000u);
-}
-__host__ __device__ __forceinline__ uint32_t odd_bytes(uint32_t w0, uint32_t w1) {
-  return ((w0 >> 8) & 0xFFu) | ((w0 >> 16) & 0xFF00u) | ((w1 << 8) & 0xFF0000u) | (w1 & 0xFF000000u);
+// bits [off, off + width) of x, 0 < width
+__host__ __device__ __forceinline__ uint32_t bits_of(uint32_t x, int off, int width) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_ubfe(x, off, width);
+#else
+  return (x >> off) & (0xFFFFFFFFu >> (32 - width));
+#endif
 }
 
 // Planes lo .. lo+7 of u[16] (lo in [-7, 24]; planes below 0 read as 0) as 16-bit masks:
 // xp[q] holds plane lo + 2q in bits 0..15 and plane lo + 2q + 1 in bits 16..31.
 __host__ __device__ __forceinline__ void plane_window(const uint32_t (&u)[16], int lo, uint32_t (&xp)[4]) {
   const int off = lo < 0 ? 0 : lo, ls = off - lo;
-  const uint32_t mk = 0xFFu >> ls;
   uint32_t D[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     uint32_t acc = 0u;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc |= ((u[4 * q + i] >> off) & mk) << (8 * i + ls);
+    for (int i = 0; i < 4; ++i) acc |= bits_of(u[4 * q + i], off, 8 - ls) << (8 * i + ls);
     D[q] = acc;
   }
   transpose8(D[0], D[1]);  // coefficients 0..7: byte p = plane lo + p
   transpose8(D[2], D[3]);  // coefficients 8..15
-  xp[0] = interleave_lo(D[0], D[2]);
-  xp[1] = interleave_hi(D[0], D[2]);
-  xp[2] = interleave_lo(D[1], D[3]);
-  xp[3] = interleave_hi(D[1], D[3]);
+  xp[0] = byte_perm<0x05010400u>(D[2], D[0]);  // planes lo, lo + 1: bytes 0 and 1 of both
+  xp[1] = byte_perm<0x07030602u>(D[2], D[0]);
+  xp[2] = byte_perm<0x05010400u>(D[3], D[1]);
+  xp[3] = byte_perm<0x07030602u>(D[3], D[1]);
 }
 
-// The inverse: u[k] |= bits of coefficient k in planes lo .. lo+7 held as plane_window does
-__host__ __device__ __forceinline__ void plane_unwindow(const uint32_t (&xp)[4], int lo, uint32_t (&u)[16]) {
-  uint32_t A0 = even_bytes(xp[0], xp[1]), A1 = even_bytes(xp[2], xp[3]);  // coefficients 0..7
-  uint32_t B0 = odd_bytes(xp[0], xp[1]), B1 = odd_bytes(xp[2], xp[3]);    // coefficients 8..15
+// The inverse, out of negabinary: q[k] += the value of coefficient k's bits in planes lo .. lo+7 held as
+// plane_window does (planes below 0 dropped).  With M = 0xAAAAAAAA a coefficient is (u ^ M) - M, which
+// splits over disjoint bits: a byte b of planes m = M's bits there gives ((b ^ m) - m) 2^lo, so the exclusive
+// or goes over four packed words and the difference into the add that places the byte.
+__host__ __device__ __forceinline__ void plane_unwindow(const uint32_t (&xp)[4], int lo, int32_t (&q)[16]) {
+  uint32_t A0 = byte_perm<0x06040200u>(xp[1], xp[0]), A1 = byte_perm<0x06040200u>(xp[3], xp[2]);  // coefficients 0..7
+  uint32_t B0 = byte_perm<0x07050301u>(xp[1], xp[0]), B1 = byte_perm<0x07050301u>(xp[3], xp[2]);  // coefficients 8..15
   transpose8(A0, A1);
   transpose8(B0, B1);
-  const uint32_t W[4] = {A0, A1, B0, B1};
-  if (lo >= 0) {
+  const uint32_t m = (lo & 1) ? 0x55555555u : 0xAAAAAAAAu;  // bit p of each byte: plane lo + p odd
+  const uint32_t W[4] = {A0 ^ m, A1 ^ m, B0 ^ m, B1 ^ m};
+  const int up = lo < 0 ? 0 : lo, down = up - lo;
+  const uint32_t c = ((m & 0xFFu) >> down) << up;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) u[k] |= ((W[k >> 2] >> (8 * (k & 3))) & 0xFFu) << lo;
-  } else {
-#pragma unroll
-    for (int k = 0; k < 16; ++k) u[k] |= ((W[k >> 2] >> (8 * (k & 3))) & 0xFFu) >> -lo;
-  }
+  for (int k = 0; k < 16; ++k)
+    q[k] = int32_t((bits_of(W[k >> 2], 8 * (k & 3) + down, 8 - down) << up) + (uint32_t(q[k]) - c));
 }
 
 // p on every active lane of the wave (WAVE), or on this lane (the CPU build of this header, which
@@ -162,6 +174,22 @@ template <bool WAVE>
 __host__ __device__ __forceinline__ bool all_lanes(bool p) {
   if constexpr (WAVE) return __builtin_amdgcn_ballot_w64(!p) == 0;
   else return p;
+}
+
+// p on any active lane of the wave (WAVE), or on this lane
+template <bool WAVE>
+__host__ __device__ __forceinline__ bool any_lane(bool p) {
+  if constexpr (WAVE) return __builtin_amdgcn_ballot_w64(p) != 0;
+  else return p;
+}
+
+// v as a value of its own, which the compiler does not move into a branch
+__host__ __device__ __forceinline__ void in_register(int& v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("" : "+v"(v));
+#else
+  (void)v;
+#endif
 }
 
 // 16 RATE bits of one block held in one (RATE <= 4) or two 64-bit words, LSB-first
@@ -190,6 +218,15 @@ struct ZBits {
       return sh ? (lo >> sh) | (hi << (64 - sh)) : lo;
     }
   }
+  // the block without its first k bits, 0 < k < 64
+  __host__ __device__ __forceinline__ void drop(int k) {
+    if constexpr (!kWide) {
+      w0 >>= k;
+    } else {
+      w0 = (w0 >> k) | (w1 << (64 - k));
+      w1 >>= k;
+    }
+  }
   __host__ __device__ __forceinline__ void clip() {
     if constexpr (kCap < 64) w0 &= (uint64_t(1) << kCap) - 1u;
     if constexpr (kCap > 64 && kCap < 128) w1 &= (uint64_t(1) << (kCap - 64)) - 1u;
@@ -207,6 +244,18 @@ struct ZfpPrep {
   bool finite;
 };
 
+// truncation, defined for every value (the blocks that are not coded pass through it too): the device's
+// conversion saturates and gives 0 for NaN
+__host__ __device__ __forceinline__ int32_t to_int(float x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  int32_t r;
+  asm("v_cvt_i32_f32 %0, %1" : "=v"(r) : "v"(x));
+  return r;
+#else
+  return int32_t(fminf(fmaxf(x, -2147483648.0f), 2147483520.0f));
+#endif
+}
+
 __host__ __device__ __forceinline__ void zfp_prepare(const float (&v)[16], ZfpPrep& z) {
   // NaN-propagating maximum of |v|: one test flags a non-finite block (coded as an empty block)
   float amax = fabsf(v[0]);
@@ -219,10 +268,9 @@ __host__ __device__ __forceinline__ void zfp_prepare(const float (&v)[16], ZfpPr
   e = e < -126 ? -126 : e;
   z.e = e;
   int32_t q[16];
-  // exact scaling and truncation (|q| < 2^30 for a coded block; the clamp only keeps the
-  // conversion defined for the blocks that are not coded)
+  // exact scaling and truncation (|q| < 2^30 for a coded block)
 #pragma unroll
-  for (int k = 0; k < 16; ++k) q[k] = int32_t(fminf(fmaxf(ldexpf(v[k], 30 - e), -2147483648.0f), 2147483520.0f));
+  for (int k = 0; k < 16; ++k) q[k] = to_int(ldexpf(v[k], 30 - e));
 #pragma unroll
   for (int j = 0; j < 4; ++j) zfp_fwd4(q[4 * j], q[4 * j + 1], q[4 * j + 2], q[4 * j + 3]);
 #pragma unroll
@@ -300,10 +348,10 @@ __host__ __device__ __forceinline__ int zfp_encode_block(const float (&v)[16], c
 }
 
 // First half of the decoder: the bit planes of a block's 16 RATE bits w (LSB-first, words past
-// the block 0) into the negabinary coefficients u (sequency order) and the block exponent e; an
-// empty block gives u = 0.
+// the block 0) into the coefficients q (sequency order) and the block exponent e; an empty block gives
+// q = 0.
 template <int RATE, bool WAVE = true>
-__host__ __device__ __forceinline__ void zfp_decode_planes(const uint32_t (&w)[4], const ZfpTables& tb, uint32_t (&u)[16],
+__host__ __device__ __forceinline__ void zfp_decode_planes(const uint32_t (&w)[4], const ZfpTables& tb, int32_t (&q)[16],
                                                            int& e) {
   constexpr int CAP = ZBits<RATE>::kCap;
   ZBits<RATE> st;
@@ -311,7 +359,7 @@ __host__ __device__ __forceinline__ void zfp_decode_planes(const uint32_t (&w)[4
   st.w1 = uint64_t(w[2]) | (uint64_t(w[3]) << 32);
   st.clip();
 #pragma unroll
-  for (int k = 0; k < 16; ++k) u[k] = 0u;
+  for (int k = 0; k < 16; ++k) q[k] = 0;
   e = 0;
   if (!(st.w0 & 1u)) return;
   e = int((st.w0 >> 1) & 0xFFu) - 127;
@@ -319,72 +367,76 @@ __host__ __device__ __forceinline__ void zfp_decode_planes(const uint32_t (&w)[4
   const uint64_t lead = st.window(9);
   const int z = lead ? __builtin_ctzll(lead) : 64;
   int o = 9 + z, n = 0;
+  if (z > 31 || o >= CAP) return;
+  st.drop(o);  // from here on st starts at the plane's first bit; past the budget it holds zeros
   for (int P0 = 31 - z; P0 >= 0 && o < CAP; P0 -= 8) {
     uint32_t xp[4] = {0u, 0u, 0u, 0u};
+    // Eight planes with no branch per lane: a lane whose budget is spent reads zeros, which give an
+    // empty plane, and planes below 0 fall out in plane_unwindow.
 #pragma unroll
     for (int p = 7; p >= 0; --p) {
-      if (P0 - 7 + p >= 0 && o < CAP) {
-        const uint64_t win = st.window(o);
+      if (any_lane<WAVE>(o < CAP)) {
+        const uint32_t wl = uint32_t(st.w0);
         uint32_t x;
+        int adv;
         if (all_lanes<WAVE>(n >= 14)) {
           // at most two candidates left.  n >= 15: the plane's 16 bits (for n = 15 the last
           // candidate's test bit is its bit; a 1 read inside the budget implies the 1).  n = 14:
           // test bit t; after a 1, coefficient 14's bit r0, and after a 1 there the test r1 for
           // coefficient 15 (its 1 implied); after r0 = 0 coefficient 15's 1 is implied if r0 lay
           // inside the budget
-          const uint32_t wl = uint32_t(win);
           const uint32_t t = (wl >> 14) & 1u, r0 = (wl >> 15) & 1u, r1 = (wl >> 16) & 1u;
           const uint32_t V = wl & 0x3FFFu;
           const bool fits = o + 16 <= CAP, two = n == 14;
-          const uint32_t x14 = !t ? V : (r0 ? (V | (1u << 14) | (r1 << 15)) : (V | (fits ? 1u << 15 : 0u)));
-          x = two ? x14 : (wl & 0xFFFFu);
-          o += two ? (!t ? 15 : (r0 ? 17 : 16)) : 16;
-          n = two ? (!t ? 14 : (r0 ? (r1 ? 16 : 15) : 16)) : (((wl >> 15) & 1u) ? 16 : n);
+          // bits 14 and 15: r0, and (r0 ? r1 : fits), after a 1 in t
+          const uint32_t c14 = t & r0, c15 = t & (r0 ? r1 : uint32_t(fits));
+          x = two ? (V | (c14 << 14) | (c15 << 15)) : (wl & 0xFFFFu);
+          adv = two ? int(15 + t + c14) : 16;
+          n = two ? int(14 + t + (t & ((r0 ^ 1u) | r1))) : (r0 ? 16 : n);
         } else {
-          const uint32_t V = uint32_t(win) & ((1u << n) - 1u);
-          const uint32_t rest = uint32_t(win >> (n + 1));
+          const uint32_t rest = uint32_t(st.w0 >> (n + 1));
+          const bool go = ((1u << n) & wl & 0xFFFFu) != 0u;  // the first test's bit (none for n = 16)
           // runs of ones by the parity of their start
           const uint32_t st0 = rest & ~(rest << 1);
           const uint32_t ae = rest + (st0 & 0x55555555u), ao = rest + (st0 & 0xAAAAAAAAu);
-          const uint32_t re = rest & ~ae;                           // ones of even-start runs
-          const uint32_t data1 = rest & ~(re ^ 0x55555555u);         // data ones: even offset in their run
+          const uint32_t data1 = rest & (ae ^ 0x55555555u);  // data ones: even offset in their run
           // the zero after an odd-length run (the closing test): after an even-start run at an odd
           // position, after an odd-start run at an even position
           const uint32_t close = bsel(0x55555555u, ao, ae) & ~rest;
-          const int e1 = close ? __builtin_ctz(close) : 32;
-          const uint32_t below = e1 >= 32 ? ~0u : (1u << e1) - 1u;
+          const uint32_t below = go ? (close - 1u) & ~close : 0u;  // the bits before it (all if there is none)
           const uint32_t dm = data1 & below;
-          const int dcount = e1 - (__builtin_popcount(rest & below) - __builtin_popcount(dm));
-          const int pc0 = __builtin_popcount(dm & 0xFFu), pc1 = __builtin_popcount(dm & 0xFFFFu),
-                    pc2 = __builtin_popcount(dm & 0xFFFFFFu);
-          const uint32_t y = uint32_t(tb.unspread[dm & 0xFFu]) | (uint32_t(tb.unspread[(dm >> 8) & 0xFFu]) << (8 - pc0)) |
-                             (uint32_t(tb.unspread[(dm >> 16) & 0xFFu]) << (16 - pc1)) |
-                             (uint32_t(tb.unspread[dm >> 24]) << (24 - pc2));
-          const int L = 15 - n;  // explicit candidates before the last one (n < 16 here)
-          const bool implied = dcount > L;
-          const uint32_t yl = y & ((1u << L) - 1u);
-          const int glen = implied ? 1 + L + __builtin_popcount(yl) : e1 + 2;
-          const bool fits = o + n + glen <= CAP;
-          const uint32_t yn = implied ? (yl | (fits ? 1u << L : 0u)) : y;
-          const bool t0 = (uint32_t(win) >> n) & 1u;  // n < 16
-          const bool all = n == 16;  // lanes whose candidates are all significant: 16 verbatim bits
-          x = all ? (uint32_t(win) & 0xFFFFu) : (t0 ? V | (yn << n) : V);
-          o += all ? 16 : (t0 ? n + glen : n + 1);
-          n = all ? 16 : (t0 ? (implied ? 16 : n + dcount) : n);
+          const int e1 = __builtin_popcount(below);
+          // n plus the explicit candidates: zeros and data ones before the closing test
+          const int nd = __builtin_popcount(dm) + (__builtin_popcount(~rest & below) + n);
+          // a byte's ones move down by the ones below it, up by its place: by the zeros below it
+          const uint32_t y = uint32_t(tb.unspread[dm & 0xFFu]) |
+                             (uint32_t(tb.unspread[(dm >> 8) & 0xFFu]) << __builtin_popcount(~dm & 0xFFu)) |
+                             (uint32_t(tb.unspread[(dm >> 16) & 0xFFu]) << __builtin_popcount(~dm & 0xFFFFu)) |
+                             (uint32_t(tb.unspread[dm >> 24]) << __builtin_popcount(~dm & 0xFFFFFFu));
+          const uint32_t yl = (y << n) & 0x7FFFu;  // candidates before the last one, in place
+          // past coefficient 14 the last candidate's 1 is implied if the bits up to it are in the budget
+          const bool implied = nd > 15;
+          int ai = __builtin_popcount(yl) + 16, an = n + 1 + e1 + int(go);
+          in_register(ai);  // both sides computed, then selected: no branch
+          in_register(an);
+          adv = implied ? ai : an;
+          x = (wl & ((1u << n) - 1u)) | yl | (implied && go && o + adv <= CAP ? 0x8000u : 0u);
+          n = nd < 16 ? nd : 16;
         }
+        o += adv;
+        st.drop(adv);
         xp[p >> 1] |= x << (16 * (p & 1));
       }
     }
-    plane_unwindow(xp, P0 - 7, u);
+    plane_unwindow(xp, P0 - 7, q);
   }
 }
 
-// Second half, without a branch: negabinary to two's complement, inverse transform, scaling.
-// v[4 j + i]: channel i of token j.
-__host__ __device__ __forceinline__ void zfp_decode_finish(const uint32_t (&u)[16], int e, float (&v)[16]) {
+// Second half, without a branch: inverse transform, scaling.  v[4 j + i]: channel i of token j.
+__host__ __device__ __forceinline__ void zfp_decode_finish(const int32_t (&s)[16], int e, float (&v)[16]) {
   int32_t q[16];
 #pragma unroll
-  for (int k = 0; k < 16; ++k) q[kZfpOrder[k]] = int32_t((u[k] ^ 0xAAAAAAAAu) - 0xAAAAAAAAu);
+  for (int k = 0; k < 16; ++k) q[kZfpOrder[k]] = s[k];
 #pragma unroll
   for (int i = 0; i < 4; ++i) zfp_inv4(q[i], q[4 + i], q[8 + i], q[12 + i]);
 #pragma unroll
@@ -395,10 +447,10 @@ __host__ __device__ __forceinline__ void zfp_decode_finish(const uint32_t (&u)[1
 
 template <int RATE, bool WAVE = true>
 __host__ __device__ __forceinline__ void zfp_decode_block(const uint32_t (&w)[4], const ZfpTables& tb, float (&v)[16]) {
-  uint32_t u[16];
+  int32_t q[16];
   int e;
-  zfp_decode_planes<RATE, WAVE>(w, tb, u, e);
-  zfp_decode_finish(u, e, v);
+  zfp_decode_planes<RATE, WAVE>(w, tb, q, e);
+  zfp_decode_finish(q, e, v);
 }
 
 // a block's 2 RATE bytes to / from the cache (blocks start at multiples of 2 RATE bytes)
