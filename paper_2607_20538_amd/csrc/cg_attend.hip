@@ -1234,11 +1234,14 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
+          const int r = 16 * i + 4 * w + gq;
+          // rows past the chunk repeat its last one with weight 0: zeros, since 0 times an infinity is not 0
+          const uint32_t live = r < nc ? 0xffffffffu : 0u;
           float x[8];
-          lo_hi(vr[i], x);
+          lo_hi(make_uint4(vr[i].x & live, vr[i].y & live, vr[i].z & live, vr[i].w & live), x);
 #pragma unroll
           for (int jj = 0; jj < JQ; ++jj) {
-            const float p = rs[jj][16 * i + 4 * w + gq];
+            const float p = rs[jj][r];
 #pragma unroll
             for (int e = 0; e < 8; ++e) va[jj][e] = fmaf(p, x[e], va[jj][e]);
           }

@@ -50,9 +50,12 @@ def _encode_rows(oc, s, X, G, T_cap, lens):
     return {k: None if rows[0][k] is None else np.concatenate([r[k] for r in rows], axis=1) for k in rows[0]}
 
 
-def _setup(oc, T, T_cap, L=1, B=2, H=2, d=128, g=32, grp=4, kind=O.GAUGE_HAAR, seed=0xA77, lens=None):
+def _setup(oc, T, T_cap, L=1, B=2, H=2, d=128, g=32, grp=4, kind=O.GAUGE_HAAR, seed=0xA77, lens=None, edit=None):
+    """edit(K, V): changes the tokens (bf16 bit patterns) before they are encoded."""
     w = synth.Workload("att", L=L, B=B, H=H, T=T, d=d, dtype="bf16", g=g, backend="bu", bits=4, data_seed=seed)
     K, V = synth.kv_tensor(w, 0), synth.kv_tensor(w, 1)
+    if edit:
+        edit(K, V)
     G = O.gauge_make(kind, L, H, d, g, seed=seed + 1)
     shp = cg.shape(L, H, d, g)
     Gd = cg.alloc_gauge(shp)
@@ -231,3 +234,30 @@ def test_attend_error_free_cache_equals_attention_on_x(kernels):
         q[:, None, :], K.repeat_interleave(4, dim=0), V.repeat_interleave(4, dim=0), scale=scale)[:, 0]
     vmax = V.abs().amax(dim=(1, 2)).repeat_interleave(4).numpy()
     _check(got[0, 0], ref.numpy(), vmax)
+
+
+BF16_INF, BF16_NEG_INF = 0x7F80, 0xFF80
+
+
+@pytest.mark.parametrize("oc,T", [
+    (O.Codec(backend=O.KIVI, bits=3, key_tokens=32, val_channels=64, residual=32), 205),
+    (O.Codec(backend=O.BLOCK_UNIFORM, bits=4, block_c=64, block_t=16), 201),
+    (O.Codec(backend=O.BLOCK_UNIFORM, bits=4, block_c=128, block_t=16), 201)], ids=["kivi", "tile64", "tile128"])
+def test_attend_infinite_value_in_the_newest_token(kernels, oc, T):
+    """An infinite channel of the newest (raw) value token is infinite in the output, as attention over
+    the decoded cache gives it, and the other channels are those of the finite tokens."""
+    def edit(K, V):
+        V[:, :, 0, T - 1, 5] = BF16_INF
+        V[:, :, 1, T - 1, 77] = BF16_NEG_INF
+
+    lens = [T, T]
+    scale = 1.0 / np.sqrt(128)
+    plain = _setup(oc, T, 224, lens=lens)
+    st = _setup(oc, T, 224, lens=lens, edit=edit)
+    ref = O.attend(oc, plain["G"], plain["kh"], plain["vh"], plain["qf"], lens, scale)
+    got, err = _attend_gpu(st, oc, lens, scale)
+    assert err == 0
+    assert np.isposinf(got[:, :, :4, 5]).all() and np.isneginf(got[:, :, 4:, 77]).all()
+    got[:, :, :4, 5] = ref[:, :, :4, 5]
+    got[:, :, 4:, 77] = ref[:, :, 4:, 77]
+    _check(got, ref, _vmax(plain, oc, lens, 4))
