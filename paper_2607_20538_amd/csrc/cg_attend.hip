@@ -448,9 +448,12 @@ __global__ __launch_bounds__(kAThreads) void att_generic(AttendDev a, GaugeDev G
   const size_t pstride = size_t(2 + 2 * d);
   for (int jj = 0; jj < nj; ++jj) {
     float* P = a.part + ((((size_t(lv) * B + b) * a.Hq + hq0 + jj) * a.nsplit) + sp) * pstride;
+    // a split without a finite score adds nothing (its sums hold exp(-inf + inf), no numbers): zeros
+    const bool none = st[jj] == -INFINITY;
     for (int idx = tid; idx < 2 + (a.raw ? 2 : 1) * d; idx += kAThreads) {
       float v;
       if (idx == 0) v = st[jj];
+      else if (none) v = 0.0f;
       else if (idx == 1) v = st[kJQ + jj];
       else if (idx < 2 + d) v = macc[jj * d + idx - 2];
       else v = maccr[jj * d + idx - 2 - d];
@@ -465,7 +468,8 @@ __global__ __launch_bounds__(kAThreads) void att_generic(AttendDev a, GaugeDev G
 // Bound by latency (a few KB per workgroup): the splits' maxima and sums are read by one lane each
 // and reduced in the wave, their weights exp(m - M) kept in LDS, and every thread then folds two
 // neighbouring channels over the splits with independent reads.  The partials' raw halves are read
-// only where a cache has raw positions (a.raw).  8 rows x 6 splits (one layer, 1500 positions): 23 -> 8 us;
+// only where a cache has raw positions (a.raw).  A split without a finite score (maximum -inf) weighs 0
+// and has written zeros, so nothing is left of it.  8 rows x 6 splits (one layer, 1500 positions): 23 -> 8 us;
 // 512 rows x 4 splits: 36 -> 13 us.
 __global__ __launch_bounds__(kAThreads) void att_combine(AttendDev a, GaugeDev G) {
   extern __shared__ float sm[];
@@ -1347,9 +1351,11 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
   const size_t pstride = size_t(2 + 2 * kD);
   for (int jj = 0; jj < nj; ++jj) {
     float* P = a.part + ((((size_t(lv) * B + b) * a.Hq + hq0 + jj) * a.nsplit) + sp) * pstride;
+    const bool none = mm[0][jj] == -INFINITY;  // no finite score: zeros, as in att_generic
     for (int idx = threadIdx.x; idx < 2 + (RAW ? 2 : 1) * kD; idx += kAThreads) {
       float v;
       if (idx == 0) v = mm[0][jj];
+      else if (none) v = 0.0f;
       else if (idx == 1) v = mm[1][jj];
       else if (idx < 2 + kD) v = macc[jj][idx - 2];
       else v = accr[jj < RJ ? jj : 0][(idx - 2 - kD) % (RAW ? kD : 1)];

@@ -261,3 +261,27 @@ def test_attend_infinite_value_in_the_newest_token(kernels, oc, T):
     got[:, :, :4, 5] = ref[:, :, :4, 5]
     got[:, :, 4:, 77] = ref[:, :, 4:, 77]
     _check(got, ref, _vmax(plain, oc, lens, 4))
+
+
+def test_attend_split_without_a_finite_score():
+    """A split whose positions all score -inf (raw keys with an infinite channel) adds nothing: the row
+    is attention over its other splits.  Heads of 64 channels, on the general kernel."""
+    d, T = 64, 300
+    oc = O.Codec(backend=O.KIVI, bits=4, key_tokens=32, val_channels=32, residual=128)
+    T0 = 192                                   # first position of the second split, in the window
+
+    def edit(K, V):
+        K[:, :, :, T0:, 0] = BF16_NEG_INF
+
+    st = _setup(oc, T, 320, B=1, H=1, d=d, g=16, edit=edit, lens=[T])
+    assert cg.attend_workspace_bytes(st["shp"], 1, 1, 4, T) == 4 * 2 * (2 + 2 * d) * 4  # two splits
+    st["q"][..., 0] = 0x3F80                   # 1.0
+    st["qf"][..., 0] = 1.0
+    scale = 1.0 / np.sqrt(d)
+    K = O.kv_decode(oc, 0, st["G"], st["kh"], 0, T, lens=[T], out_bf16=False)[0, 0, 0, :T0].astype(np.float64)
+    V = O.kv_decode(oc, 1, st["G"], st["vh"], 0, T, lens=[T], out_bf16=False)[0, 0, 0, :T0].astype(np.float64)
+    p = np.exp(scale * (st["qf"][0, 0].astype(np.float64) @ K.T))
+    ref = (p @ V / p.sum(-1, keepdims=True))[None, None]
+    got, err = _attend_gpu(st, oc, [T], scale, lens_dev=False)
+    assert err == 0
+    _check(got, ref, np.full((1, 1, 4), np.abs(V).max()))
