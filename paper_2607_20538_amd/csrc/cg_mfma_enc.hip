@@ -103,6 +103,81 @@ constexpr int kModePass = 1;   // error-free backend: binary32 z
 constexpr int kModeKeys = 2;   // KIVI keys: one block per channel over a 32-token group
 constexpr int kModeZfp = 3;    // zfp-style fixed-rate blocks of 4 tokens x 4 channels (BITS = rate)
 
+// Set in a lane's flags for a block with a non-finite z (not a flag of the interface)
+constexpr int kFlagRecode = 1 << 16;
+
+// Codes the token rows of a 32-token tile that have a non-finite (or huge, at least 2^100) channel as the
+// general kernel does: z by the binary32 FMA chain over the channel's own group, ranges that leave NaN
+// out.  The matrix cores' products span 32 or more channels in three planes, where 0 times an infinity or
+// NaN and infinities of two signs are NaN, which would spoil the other groups and blocks of the token.
+// x: the tile's first token, pitch tstride; nlive rows; codes and side: the tile's first row.  flagged
+// (kTok) and z (kD): LDS.  All threads of the workgroup.
+template <int BITS, int NB>
+__device__ int recode_rows(const MfmaArgs& a, const char* x, int64_t tstride, int nlive, int l, int h, uint8_t* codes,
+                           uint32_t* side, int* flagged, float* z) {
+  constexpr int RB = kD * BITS / 8, NBK = kD / NB, CW = NB * BITS / 32;
+  const int tid = int(threadIdx.x), g = a.g;
+  int flags = 0;
+  __syncthreads();  // the row before (or the staged tiles) is read
+  if (tid < kTok) flagged[tid] = 0;
+  __syncthreads();
+  {
+    const int t = tid >> 3, c16 = tid & 7;  // 16 channels of a row
+    if (t < nlive) {
+      bool odd = false;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const u32x4_t v = *(const u32x4_t*)(x + t * tstride + 32 * c16 + 16 * i);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t lo = (v[e] >> 7) & 0xffu, hi = (v[e] >> 23) & 0xffu;  // exponents
+          odd = odd || lo >= 227u || hi >= 227u;
+          if (lo == 255u || hi == 255u) flags |= CG_FLAG_NONFINITE;
+        }
+      }
+      if (odd) flagged[t] = 1;
+    }
+  }
+  __syncthreads();
+  for (int t = 0; t < nlive; ++t) {
+    if (!flagged[t]) continue;
+    if (tid < kD) {
+      const int r = tid / g;
+      const float* row = a.g32 + (((size_t(l) * 2 + a.s) * a.Hg + h) * a.R + r) * g * g + size_t(tid - r * g) * g;
+      const uint16_t* xr = (const uint16_t*)(x + t * tstride) + r * g;
+      float acc = 0.0f;
+      for (int k = 0; k < g; ++k) acc = fmaf(row[k], bf16_to_f32(xr[k]), acc);
+      z[tid] = acc;
+    }
+    __syncthreads();
+    if (tid < NBK) {
+      const float* zb = z + tid * NB;
+      float mn = zb[0], mx = zb[0];
+      for (int e = 1; e < NB; ++e) {
+        mn = fminf(mn, zb[e]);
+        mx = fmaxf(mx, zb[e]);
+      }
+      const Side sd = make_side(mn, mx, BITS);
+      uint32_t* dst = (uint32_t*)(codes + size_t(t) * RB) + tid * CW;
+      uint64_t acc = 0;
+      int nbit = 0, wi = 0;
+      for (int e = 0; e < NB; ++e) {
+        acc |= uint64_t(quantize(zb[e], sd.mn, sd.inv, float((1 << BITS) - 1))) << nbit;
+        nbit += BITS;
+        if (nbit >= 32) {
+          dst[wi++] = uint32_t(acc);
+          acc >>= 32;
+          nbit -= 32;
+        }
+      }
+      side[size_t(t) * NBK + tid] = sd.word;
+      flags |= sd.flags;
+    }
+    __syncthreads();
+  }
+  return flags;
+}
+
 // Software pipeline over 32-token tiles, one barrier per tile.  Iteration t:
 //   1. block-range partials of tile t from its accumulator (64-channel blocks: wave-pair
 //      exchange through red[t & 1]);
@@ -115,7 +190,8 @@ constexpr int kModeZfp = 3;    // zfp-style fixed-rate blocks of 4 tokens x 4 ch
 // contiguous run of 32 RB bytes in the cache and its side words one run of 32 NBK words, so
 // the staged copy leaves with whole-line stores instead of 32 scattered row pieces.
 // PAGED: the cache is a page pool; the rows of a tile (always inside one page) go to the page its
-// positions map to, looked up one tile ahead of the tile's first use.
+// positions map to, looked up one tile ahead of the tile's first use.  Blocks with a non-finite value are
+// coded again after the range (recode_rows).
 template <int NP, int KS, int BITS, int NB, int MODE, int TB = 1, bool PAGED = false>
 __global__ __launch_bounds__(kThreads, NP == 2 ? 3 : 2) void enc_mfma(MfmaArgs a) {
   constexpr bool PASS = MODE == kModePass, KEYS = MODE == kModeKeys, ZFP = MODE == kModeZfp;
@@ -254,6 +330,10 @@ __global__ __launch_bounds__(kThreads, NP == 2 ? 3 : 2) void enc_mfma(MfmaArgs a
     return int64_t((size_t(l) * a.cB + pg) * a.cH + h) * a.T_cap + (a.t0 + tile * kTok) % a.T_cap;
   };
   int64_t prow[2] = {-1, -1};
+  __shared__ int recode;  // PAGED: the workgroup met a non-finite z
+  if constexpr (PAGED) {
+    if (threadIdx.x == 0) recode = 0;  // a barrier follows in every step
+  }
   if constexpr (PAGED) prow[0] = page_row(tb, page_of(tb));
   // staged tile -> cache: thread i stores 16-byte granule i of the codes (row i / BITS) and,
   // counting from the last thread, side word i (row i / NBK); rows past the view are skipped
@@ -490,7 +570,7 @@ __global__ __launch_bounds__(kThreads, NP == 2 ? 3 : 2) void enc_mfma(MfmaArgs a
 #pragma unroll
         for (int i = 0; i < BITS; ++i) dst[i] = words[i];
       }
-      if (live) flags |= sd.flags | (bad ? CG_FLAG_NONFINITE : 0);
+      if (live) flags |= PAGED ? (bad ? kFlagRecode : sd.flags) : (sd.flags | (bad ? CG_FLAG_NONFINITE : 0));
       if constexpr (TILE) {
         if (hc == 0 && (n & 15) == 0 && w % (NB / 32) == 0) sstage[P][(n >> 4) * NBK + w / (NB / 32)] = sd.word;
       } else if constexpr (NB == 16) {
@@ -509,12 +589,27 @@ __global__ __launch_bounds__(kThreads, NP == 2 ? 3 : 2) void enc_mfma(MfmaArgs a
   }
   if constexpr (QUANT) {
     // the last tile's staging: every wave's LDS writes done, then the final contiguous stores
+    if (PAGED && (flags & kFlagRecode)) recode = 1;
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(63));
     __builtin_amdgcn_s_barrier();
     if ((te - tb) & 1) flush(te - 1, std::integral_constant<int, 0>());
     else flush(te - 1, std::integral_constant<int, 1>());
   }
-  if constexpr (!PAGED) ring_copy();
+  if constexpr (PAGED) {
+    if (recode) {
+      flags &= ~kFlagRecode;
+      __builtin_amdgcn_s_waitcnt(waitcnt_imm(0));  // this wave's stores, before those over them
+      for (int tile = tb; tile < te; ++tile) {
+        const int64_t row = page_row(tile, page_of(tile));
+        if (row < 0) continue;
+        flags |= recode_rows<BITS, NB>(a, xs + int64_t(tile) * kTok * tstride, tstride, min(kTok, a.T - tile * kTok), l,
+                                       h, a.codes + size_t(row) * RB, a.side + size_t(row) * NBK, (int*)xtile[0],
+                                       (float*)xtile[1]);
+      }
+    }
+  } else {
+    ring_copy();
+  }
   if (flags && a.err) atomicOr(a.err, flags);
 }
 

@@ -111,3 +111,74 @@ def test_pages_outside_the_pool_are_skipped(tiles, monkeypatch):
         assert not b[:, int(table[r, i])].any()
         a[:, int(table[r, i])] = 0
     assert torch.equal(a, b)
+
+
+def _paged(X, table, P, Gd, shp, oc, pool_pages, w):
+    pool = cg.Cache(oc, 0, w.L, pool_pages, w.H, P, 128)
+    err = torch.zeros(1, dtype=torch.int32, device="cuda")
+    pt = torch.from_numpy(table).cuda()
+    cg.kv_encode_paged(0, X, cg.page_table(pt, P), Gd, shp, oc, pool, 0, err)
+    torch.cuda.synchronize()
+    return pool.codes.clone(), pool.side.clone(), int(err.item())
+
+
+BAD = [float("nan"), float("inf"), float("-inf"), "two"]
+
+
+def _spoil(X, g, bad):
+    """Three tokens with non-finite channels: one channel, one whole group, one whole token."""
+    X = X.clone()
+    v = float("inf") if bad == "two" else bad
+    X[0, 0, 0, 33, g // 2] = v
+    X[0, 1, 1, 70, 64:64 + g] = v
+    X[0, 1, 0, 5] = v
+    if bad == "two":                          # infinities of both signs in one group
+        X[0, 0, 0, 33, g // 2 + 1] = -v
+    return X
+
+
+@pytest.mark.parametrize("tiles", [None, 4])
+@pytest.mark.parametrize("bad", BAD)
+@pytest.mark.parametrize("g,bits,n", [(8, 4, 64), (16, 3, 32), (16, 8, 16), (32, 2, 64), (64, 6, 32), (128, 4, 64)])
+def test_non_finite_tokens_as_the_general_kernel_codes_them(g, bits, n, bad, tiles, monkeypatch):
+    """With the identity gauge z = x on both kernels, so every code and side word is the same, also of the
+    blocks and groups that hold a non-finite channel (a side word that is no number: of either sign), and
+    the flags are."""
+    monkeypatch.delenv("CG_KERNELS", raising=False)
+    monkeypatch.delenv("CG_TILES_PER_WG", raising=False)
+    if tiles:
+        monkeypatch.setenv("CG_TILES_PER_WG", str(tiles))
+    P, T = 64, 160
+    oc = cg.Codec(cg.BLOCK_UNIFORM, bits, n)
+    _, _, _, w, table, pool_pages, _ = _setup(g, T, P)
+    shp = cg.shape(w.L, w.H, 128, g)
+    Gd = cg.alloc_gauge(shp)
+    cg.gauge_make(cg.GAUGE_IDENTITY, shp, G_host=None, G_dev=Gd)
+    # binary32 tokens take the general kernel's binary32 chain
+    X = _spoil(x_dev(synth.kv_tensor(w, 0)), g, bad)
+    want = _paged(X.float(), table, P, Gd, shp, oc, pool_pages, w)
+    got = _paged(X, table, P, Gd, shp, oc, pool_pages, w)
+    assert want[2] & cg.CG_FLAG_NONFINITE and got[2] == want[2]
+    assert torch.equal(got[0], want[0])
+    assert torch.allclose(got[1].view(torch.float16), want[1].view(torch.float16), rtol=0, atol=0, equal_nan=True)
+
+
+@pytest.mark.parametrize("bad", BAD)
+@pytest.mark.parametrize("g", [8, 16, 32])
+def test_non_finite_channels_leave_other_groups_alone(g, bad):
+    """Blocks of other groups keep the bytes that they have beside finite tokens."""
+    P, T, n = 64, 160, 16
+    oc = cg.Codec(cg.BLOCK_UNIFORM, 4, n)
+    _, Gd, shp, w, table, pool_pages, _ = _setup(g, T, P)
+    X = x_dev(synth.kv_tensor(w, 0))
+    clean = _paged(X, table, P, Gd, shp, oc, pool_pages, w)
+    got = _paged(_spoil(X, g, bad), table, P, Gd, shp, oc, pool_pages, w)
+    assert clean[2] == 0 and got[2] & cg.CG_FLAG_NONFINITE
+    keep = torch.ones((pool_pages, w.H, P, 128 // n), dtype=torch.bool, device="cuda")
+    m = max(g, n)
+    keep[int(table[0, 0]), 0, 33, : m // n] = False
+    keep[int(table[1, 1]), 1, 70 - P, 64 // n:(64 + m) // n] = False
+    keep[int(table[1, 0]), 0, 5] = False
+    for a, b in zip(got[:2], clean[:2]):
+        a, b = (t[: keep.numel() * (t.numel() // keep.numel())].view(*keep.shape, -1) for t in (a, b))
+        assert torch.equal(a[keep], b[keep])
