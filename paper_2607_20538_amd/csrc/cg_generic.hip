@@ -20,6 +20,7 @@
 #include "cg_internal.h"
 #include "cg_device.h"
 #include "cg_general.h"
+#include "cg_recode.h"
 #include "cg_zfp.h"
 
 namespace cg {
@@ -172,12 +173,16 @@ constexpr bool general_planes(int kr, int nbw, int store) {
   return store == kStoreRows && kr > 0 && kr % 8 == 0 && kr * nbw <= 64;
 }
 
-// PL: bf16 tokens stay bf16 in LDS and the gauge runs as three bf16 planes
+// PL: bf16 tokens stay bf16 in LDS and the gauge runs as three bf16 planes; rows with a non-finite channel
+// are coded again after the range (recode_rows)
 template <int KR, int NBW, int STORE, bool PL>
 __global__ __launch_bounds__(kThreads, general_waves(KR, NBW, STORE)) void enc_general(EncArgs a) {
   static_assert(!PL || general_planes(KR, NBW, STORE), "groups of 32 KK channels");
-  extern __shared__ float sm[];
+  // the alignment matters: the dynamic part starts behind the static one, and at an offset of 4 every 16-byte
+  // access to the tiles is misaligned (16 layers x 2 x 8 heads x 2048 tokens of 64 channels: 41 -> 77 us)
+  extern __shared__ __attribute__((aligned(16))) float sm[];
   __shared__ std::conditional_t<STORE == kStoreOther, ZfpTables, char> ztab;
+  __shared__ int recode;  // PL: the workgroup met such a row
   const ViewDev& X = a.X;
   const CodecDev& c = a.c;
   const CacheDev& k = a.k;
@@ -238,17 +243,22 @@ __global__ __launch_bounds__(kThreads, general_waves(KR, NBW, STORE)) void enc_g
   float A[NBW][KR > 0 ? KR : 1];
   if constexpr (KR > 0 && !PL) gauge_operand<KR, NBW>(graw, A);
   int flags = 0;
+  // cache batch row and its position of a tile's row 0; false: a page outside the table or the pool
+  auto place = [&](int tile, int& crow, int& pos0) {
+    crow = b;
+    pos0 = a.t0 + tile * TT;
+    if (!a.pt.pages) return true;
+    const int lp = pos0 / a.pt.page_size;  // a tile never crosses a page
+    crow = lp < a.pt.max_pages ? a.pt.pages[size_t(b) * a.pt.max_pages + lp] : -1;
+    pos0 -= lp * a.pt.page_size;
+    return crow >= 0 && crow < k.B;
+  };
+  if (PL && tid == 0) recode = 0;  // set after the range, behind its barriers
   for (int tile = tb; tile < te; ++tile) {
     const int tile0 = tile * TT, ntok = min(TT, X.T - tile0);
-    int crow = b, pos0 = a.t0 + tile0;  // cache batch row and its position of tile row 0
-    bool skip = false;
-    if (a.pt.pages) {  // a tile never crosses a page
-      const int lp = pos0 / a.pt.page_size;
-      crow = lp < a.pt.max_pages ? a.pt.pages[size_t(b) * a.pt.max_pages + lp] : -1;
-      skip = crow < 0 || crow >= k.B;
-      if (skip && tid == 0 && a.err) atomicOr(a.err, CG_FLAG_POS_RANGE);
-      pos0 -= lp * a.pt.page_size;
-    }
+    int crow, pos0;
+    const bool skip = !place(tile, crow, pos0);
+    if (skip && tid == 0 && a.err) atomicOr(a.err, CG_FLAG_POS_RANGE);
     const size_t slc = (size_t(l) * k.B + crow) * k.H + h;
     // KIVI window, or rows of an unfinished tile (view rows >= tq; t0 is a multiple of bt): raw bf16
     // rows into the ring (slot = cache position mod its slots)
@@ -267,8 +277,8 @@ __global__ __launch_bounds__(kThreads, general_waves(KR, NBW, STORE)) void enc_g
         const uint32_t w[4] = {r.v[0].x, r.v[0].y, r.v[0].z, r.v[0].w};
         if (t < nq && !skip) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if ((w[e] & 0x7f80u) == 0x7f80u || (w[e] & 0x7f800000u) == 0x7f800000u) flags |= CG_FLAG_NONFINITE;
+          for (int e = 0; e < 4; ++e)  // an exponent of at least 2^100
+            if ((w[e] & 0x7f80u) >= 0x7180u || (w[e] & 0x7f800000u) >= 0x71800000u) flags |= kFlagRecode;
         }
         *reinterpret_cast<uint4*>(xb + t * xpitch + 16 * c8) = r.v[0];
         return;
@@ -337,6 +347,23 @@ __global__ __launch_bounds__(kThreads, general_waves(KR, NBW, STORE)) void enc_g
       flags |= store_rows_blocks(zs, ntok, d, dp, n, c.bits, k, slc, pos0);
     }
   }
+  if constexpr (PL) {
+    if (flags & kFlagRecode) recode = 1;
+    __syncthreads();
+    if (recode) {
+      flags &= ~kFlagRecode;
+      __builtin_amdgcn_s_waitcnt(0);  // this wave's stores, before those over them
+      for (int tile = tb; tile < te; ++tile) {
+        int crow, pos0;
+        const int nq = min(min(TT, X.T - tile * TT), kivi ? a.tq - tile * TT : TT);
+        if (!place(tile, crow, pos0) || nq <= 0) continue;
+        const size_t row0 = ((size_t(l) * k.B + crow) * k.H + h) * k.T_cap + pos0;
+        flags |= recode_rows(reinterpret_cast<const char*>(X.ptr) + 2 * (xbase + size_t(tile) * TT * X.st), 2 * X.st, nq,
+                             d, n, c.bits, a.G.f32 + gauge_block(l, s, h, 0, a.G.H, a.G.R) * a.G.g * a.G.g, a.G.g,
+                             k.codes + row0 * row_bytes, k.side + row0 * (d / n), reinterpret_cast<int*>(zs), zs + 64);
+      }
+    }
+  }
   if (flags && a.err) atomicOr(a.err, flags);
 }
 
@@ -388,7 +415,7 @@ __device__ __forceinline__ void code8_values(const Code8& c, int bits, int ch0, 
 // STORE as in the encoder: kStoreRows for codes by token rows (block-uniform, KIVI values)
 template <int KR, int NBW, int STORE>
 __global__ __launch_bounds__(kThreads, general_waves(KR, NBW, STORE)) void dec_general(DecArgs a) {
-  extern __shared__ float sm[];
+  extern __shared__ __attribute__((aligned(16))) float sm[];
   __shared__ std::conditional_t<STORE == kStoreOther, ZfpTables, char> ztab;
   const ViewDev& Y = a.Y;
   const CodecDev& c = a.c;

@@ -29,6 +29,7 @@
 #include "cg_device.h"
 #include "cg_mfma_util.h"
 #include "cg_mfma_common.h"
+#include "cg_recode.h"
 #include "cg_zfp.h"
 
 namespace cg {
@@ -102,81 +103,6 @@ constexpr int kModeBU = 0;     // block-uniform (or KIVI values: n = value chann
 constexpr int kModePass = 1;   // error-free backend: binary32 z
 constexpr int kModeKeys = 2;   // KIVI keys: one block per channel over a 32-token group
 constexpr int kModeZfp = 3;    // zfp-style fixed-rate blocks of 4 tokens x 4 channels (BITS = rate)
-
-// Set in a lane's flags for a block with a non-finite z (not a flag of the interface)
-constexpr int kFlagRecode = 1 << 16;
-
-// Codes the token rows of a 32-token tile that have a non-finite (or huge, at least 2^100) channel as the
-// general kernel does: z by the binary32 FMA chain over the channel's own group, ranges that leave NaN
-// out.  The matrix cores' products span 32 or more channels in three planes, where 0 times an infinity or
-// NaN and infinities of two signs are NaN, which would spoil the other groups and blocks of the token.
-// x: the tile's first token, pitch tstride; nlive rows; codes and side: the tile's first row.  flagged
-// (kTok) and z (kD): LDS.  All threads of the workgroup.
-template <int BITS, int NB>
-__device__ int recode_rows(const MfmaArgs& a, const char* x, int64_t tstride, int nlive, int l, int h, uint8_t* codes,
-                           uint32_t* side, int* flagged, float* z) {
-  constexpr int RB = kD * BITS / 8, NBK = kD / NB, CW = NB * BITS / 32;
-  const int tid = int(threadIdx.x), g = a.g;
-  int flags = 0;
-  __syncthreads();  // the row before (or the staged tiles) is read
-  if (tid < kTok) flagged[tid] = 0;
-  __syncthreads();
-  {
-    const int t = tid >> 3, c16 = tid & 7;  // 16 channels of a row
-    if (t < nlive) {
-      bool odd = false;
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const u32x4_t v = *(const u32x4_t*)(x + t * tstride + 32 * c16 + 16 * i);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const uint32_t lo = (v[e] >> 7) & 0xffu, hi = (v[e] >> 23) & 0xffu;  // exponents
-          odd = odd || lo >= 227u || hi >= 227u;
-          if (lo == 255u || hi == 255u) flags |= CG_FLAG_NONFINITE;
-        }
-      }
-      if (odd) flagged[t] = 1;
-    }
-  }
-  __syncthreads();
-  for (int t = 0; t < nlive; ++t) {
-    if (!flagged[t]) continue;
-    if (tid < kD) {
-      const int r = tid / g;
-      const float* row = a.g32 + (((size_t(l) * 2 + a.s) * a.Hg + h) * a.R + r) * g * g + size_t(tid - r * g) * g;
-      const uint16_t* xr = (const uint16_t*)(x + t * tstride) + r * g;
-      float acc = 0.0f;
-      for (int k = 0; k < g; ++k) acc = fmaf(row[k], bf16_to_f32(xr[k]), acc);
-      z[tid] = acc;
-    }
-    __syncthreads();
-    if (tid < NBK) {
-      const float* zb = z + tid * NB;
-      float mn = zb[0], mx = zb[0];
-      for (int e = 1; e < NB; ++e) {
-        mn = fminf(mn, zb[e]);
-        mx = fmaxf(mx, zb[e]);
-      }
-      const Side sd = make_side(mn, mx, BITS);
-      uint32_t* dst = (uint32_t*)(codes + size_t(t) * RB) + tid * CW;
-      uint64_t acc = 0;
-      int nbit = 0, wi = 0;
-      for (int e = 0; e < NB; ++e) {
-        acc |= uint64_t(quantize(zb[e], sd.mn, sd.inv, float((1 << BITS) - 1))) << nbit;
-        nbit += BITS;
-        if (nbit >= 32) {
-          dst[wi++] = uint32_t(acc);
-          acc >>= 32;
-          nbit -= 32;
-        }
-      }
-      side[size_t(t) * NBK + tid] = sd.word;
-      flags |= sd.flags;
-    }
-    __syncthreads();
-  }
-  return flags;
-}
 
 // Software pipeline over 32-token tiles, one barrier per tile.  Iteration t:
 //   1. block-range partials of tile t from its accumulator (64-channel blocks: wave-pair
@@ -602,9 +528,9 @@ __global__ __launch_bounds__(kThreads, NP == 2 ? 3 : 2) void enc_mfma(MfmaArgs a
       for (int tile = tb; tile < te; ++tile) {
         const int64_t row = page_row(tile, page_of(tile));
         if (row < 0) continue;
-        flags |= recode_rows<BITS, NB>(a, xs + int64_t(tile) * kTok * tstride, tstride, min(kTok, a.T - tile * kTok), l,
-                                       h, a.codes + size_t(row) * RB, a.side + size_t(row) * NBK, (int*)xtile[0],
-                                       (float*)xtile[1]);
+        flags |= recode_rows(xs + int64_t(tile) * kTok * tstride, tstride, min(kTok, a.T - tile * kTok), kD, NB, BITS,
+                             a.g32 + ((size_t(l) * 2 + a.s) * a.Hg + h) * a.R * a.g * a.g, a.g,
+                             a.codes + size_t(row) * RB, a.side + size_t(row) * NBK, (int*)xtile[0], (float*)xtile[1]);
       }
     }
   } else {

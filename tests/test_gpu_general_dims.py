@@ -207,3 +207,54 @@ def test_general_encoder_flags_and_keeps_neighbouring_groups():
     keep[33, 1] = False
     for codes, side in caches[1:]:
         assert torch.equal(codes[keep], caches[0][0][keep]) and torch.equal(side[keep], caches[0][1][keep])
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("d,g,n,backend", [(64, 64, 16, O.BLOCK_UNIFORM), (64, 32, 64, O.BLOCK_UNIFORM), (96, 32, 32, O.KIVI),
+                                           (80, 16, 16, O.BLOCK_UNIFORM)])
+def test_non_finite_bf16_tokens_as_binary32_ones(d, g, n, backend, bad):
+    """Token rows of bf16 tensors (three gauge planes where g is a multiple of 32): with the identity gauge
+    every byte and flag is that of the same tokens in binary32 (KIVI takes bf16 alone: of the
+    block-uniform values), also where a channel, a group or a whole token is not finite."""
+    T = 192
+    shp = cg.shape(1, 1, d, g)
+    Gd = cg.alloc_gauge(shp)
+    cg.gauge_make(cg.GAUGE_IDENTITY, shp, G_host=None, G_dev=Gd)
+    X = torch.randn((1, 1, 1, T, d), generator=torch.Generator().manual_seed(3)).to(torch.bfloat16).cuda()
+    X[0, 0, 0, 33, g // 2] = bad
+    X[0, 0, 0, 70, :g] = bad
+    X[0, 0, 0, 5] = bad
+    tq = 160 if backend == O.KIVI else T
+    out = []
+    for oc, x in ((cg.Codec(backend, 4, n, 32, n, 32), X), (cg.Codec(cg.BLOCK_UNIFORM, 4, n), X[:, :, :, :tq].float())):
+        k = cg.Cache(oc, 1, 1, 1, 1, T, d)
+        err = torch.zeros(1, dtype=torch.int32, device="cuda")
+        cg.kv_encode(1, x, Gd, shp, oc, k, err_flag=err)
+        torch.cuda.synchronize()
+        out.append((k.codes.view(T, -1)[:tq].clone(), k.side.view(T, -1)[:tq].clone(), int(err.item())))
+    assert out[0][2] == out[1][2] and out[1][2] & cg.CG_FLAG_NONFINITE
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("d,g", [(64, 32), (192, 64)])
+def test_three_plane_encoder_keeps_neighbouring_groups(d, g, bad):
+    """As above for bf16 token rows: the blocks of the other groups, and every other token, keep their bytes."""
+    T, n = 160, 16
+    oc = cg.Codec(cg.BLOCK_UNIFORM, 4, n)
+    _, Gd, shp = _gauge(O.GAUGE_HAAR, 1, 1, d, g)
+    X = torch.randn((1, 1, 1, T, d), generator=torch.Generator().manual_seed(4)).to(torch.bfloat16).cuda()
+    spoilt = X.clone()
+    spoilt[0, 0, 0, 33, 5] = bad
+    out = []
+    for x in (X, spoilt):
+        k = cg.Cache(oc, 0, 1, 1, 1, T, d)
+        err = torch.zeros(1, dtype=torch.int32, device="cuda")
+        cg.kv_encode(0, x, Gd, shp, oc, k, err_flag=err)
+        torch.cuda.synchronize()
+        assert bool(int(err.item()) & cg.CG_FLAG_NONFINITE) == (x is spoilt)
+        out.append((k.codes.view(T, d // n, -1), k.side.view(T, d // n, -1)))
+    keep = torch.ones((T, d // n), dtype=torch.bool, device="cuda")
+    keep[33, : g // n] = False
+    for a, b in zip(*out):
+        assert torch.equal(a[keep], b[keep])
