@@ -285,3 +285,19 @@ def test_attend_split_without_a_finite_score():
     got, err = _attend_gpu(st, oc, [T], scale, lens_dev=False)
     assert err == 0
     _check(got, ref, np.full((1, 1, 4), np.abs(V).max()))
+
+
+# finalize_rows and gauge_query by gauge and width: groups that are no multiple of 8 or of 4 channels, shares
+# of more rows of G_V than a thread holds, widths whose quarter does not divide the workgroup
+@pytest.mark.parametrize("T", [97, 600])       # one split, several
+@pytest.mark.parametrize("d,g", [(128, 4), (128, 2), (256, 256), (192, 192), (96, 12), (80, 80)])
+def test_attend_gauge_widths(kernels, d, g, T):
+    oc = O.Codec(backend=O.BLOCK_UNIFORM, bits=4, block_c={128: 64, 80: 80, 96: 32}.get(d, 64))
+    st = _setup(oc, T, 608, d=d, g=g, grp=6, B=1)
+    lens = [T]
+    scale = 1.0 / np.sqrt(d)
+    ref = O.attend(oc, st["G"], st["kh"], st["vh"], st["qf"], lens, scale)
+    for lens_dev in (True, False):
+        got, err = _attend_gpu(st, oc, lens, scale, lens_dev=lens_dev)
+        assert err == 0
+        _check(got, ref, _vmax(st, oc, lens, 6))
