@@ -16,10 +16,6 @@ __device__ __forceinline__ size_t gauge_block(int l, int s, int h, int r, int H,
   return ((size_t(l) * 2 + s) * H + h) * R + r;
 }
 
-__device__ __forceinline__ float load_x(const ViewDev& v, size_t off) {
-  return v.bf16 ? bf16_to_f32(((const uint16_t*)v.ptr)[off]) : ((const float*)v.ptr)[off];
-}
-
 // Channels off .. off + 7 of a view row as loaded (16-byte aligned: rows and channel offsets are), and
 // their binary32 values
 struct Raw8 {
@@ -524,14 +520,6 @@ __device__ int store_key_groups(const float* zs, int ngrp, int kg, int d, int dp
     flags |= quantize_block_to(zs + (u * kg) * dp + ch, dp, kg, bits, dst, k.side + gi * d + ch);
   }
   return flags;
-}
-
-[[maybe_unused]] __device__ void store_rows_pass(const float* zs, int ntok, int d, int dp, const CacheDev& k, size_t slc, int pos0) {
-  float* out = (float*)k.codes;
-  for (int idx = threadIdx.x; idx < ntok * d; idx += blockDim.x) {
-    const int t = idx / d, ch = idx - t * d;
-    out[(slc * k.T_cap + pos0 + t) * d + ch] = zs[t * dp + ch];
-  }
 }
 
 // ------------------------------------------------------------------------------------------
