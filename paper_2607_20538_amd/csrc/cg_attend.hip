@@ -234,7 +234,7 @@ __device__ void finalize_rows(const AttendDev& a, const GaugeDev& G, const OutRo
 constexpr int kGTile = 64;  // positions per step
 constexpr int kGAcc = 8;    // (query, channel) accumulators per thread: kJQ * d / 256 for d <= 256
 
-// Four queries per finalize_rows: its sums then fit the tile's space from 64 channels on.  All eight at
+// Four queries per finalize_rows (att_mfma too): its sums then fit the tile's space from 64 channels on.  All eight at
 // once took 32 KB and more registers, fewer workgroups per CU: 126 us against 78 for a step over 8192 positions
 // (2 layers, batch 4, 4 heads of 64 channels).
 constexpr int kGFin = 4;
@@ -750,7 +750,7 @@ __device__ __forceinline__ void gauge_query(const QueryRows& q, const GaugeDev& 
 }
 
 template <int BITS, int NBLK, int TB, bool KIVI = false>
-__global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G) {
+__global__ __launch_bounds__(kAThreads, 3) void att_mfma(AttendDev a, GaugeDev G) {
   static_assert(TB == 1 || TB == 16, "token tiles of 16");
   static_assert(!KIVI || (TB == 1 && NBLK == 2), "KIVI: 32-position key groups, 64-channel value blocks");
   constexpr bool RAW = TB > 1 || KIVI;         // raw bf16 positions after the quantised ones
@@ -781,10 +781,11 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
   // of channels 2i, 2i + 1 in word i; rows of 68 words, so the 16-byte reads of 16 tokens and the
   // word writes of 64 lanes both spread over all banks), and the side word of each channel
   constexpr int KROW = 68;
-  __shared__ __attribute__((aligned(16))) uint32_t ktk[KIVI ? 4 : 1][KIVI ? 32 * KROW : finalize_floats(JQ)];
-  // finalize_rows' sums, after the last key group
+  constexpr int FJ = JQ < kGFin ? JQ : kGFin;  // queries per finalize_rows
+  __shared__ __attribute__((aligned(16))) uint32_t ktk[KIVI ? 4 : 1][KIVI ? 32 * KROW : finalize_floats(FJ)];
+  // finalize_rows' sums (and the raw rows' of the four waves), after the last key group
   float* red = reinterpret_cast<float*>(&ktk[0][0]);
-  static_assert(!KIVI || 4 * 32 * KROW >= finalize_floats(JQ), "space of finalize_rows");
+  static_assert(sizeof(ktk) >= sizeof(float) * finalize_floats(FJ) && sizeof(ktk) >= sizeof(float) * 4 * JQ * kD, "space of the sums");
   __shared__ __attribute__((aligned(16))) uint32_t kgs[KIVI ? 4 : 1][KIVI ? kD : 1];
 
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -1157,13 +1158,17 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
   if (t0 < t_endq) step(t0, std::false_type{});
 
   // raw positions [max(tq, t_begin), t_end) of this split (staged tile tokens, at most 15; the KIVI
-  // window, at most win + 31), 64 at a time: 16 lanes read a position's key row and share its
+  // window, at most win + 31), 16 RI at a time: 16 lanes read a position's key row and share its
   // scores with the raw query (macc still holds q), a wave keeps the running maximum and sum of a
   // query, and each thread folds 8 channels of every 16th position's value row, rescaled as the
   // maximum moves.  One workgroup per row has them all, so their latency adds to the launch: with
   // one thread per position reading its row 2 bytes at a time, the 128 to 159 positions of a KIVI window
-  // were 146 of a 380 us launch (8 layers x 4 rows x 8 heads x 16000 positions, 3 bits).
+  // were 146 of a 380 us launch (8 layers x 4 rows x 8 heads x 16000 positions, 3 bits).  Tiles take one pass of 16
+  // positions, and the query stays in LDS: with it and the sums of 64 positions held, every wave of the
+  // launch had 174 registers (KIVI, tiles with n = 64) or 246 (n = 128) and a SIMD two waves.  8 x 32 x 8 rows of
+  // 16384 positions: tiles, 4 bits, n = 64 897 -> 812 us, n = 128 990 -> 897; KIVI, 3 bits, 1397 -> 1185.
   if constexpr (RAW) {
+    constexpr int RI = KIVI ? 4 : 1, CH = 16 * RI;  // value rows per thread and pass, positions per pass
     const int ringsz = KIVI ? a.win + 32 : TB;
     const int r0 = max(tq, t_begin), nr = max(0, t_end - r0);
     const size_t ring0 = ((size_t(l) * a.kc.B + b) * a.kc.H + h) * ringsz;
@@ -1172,14 +1177,6 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
       rml[1][threadIdx.x] = 0.0f;
     }
     if (nr > 0) {
-      float qv[JQ][8], va[JQ][8];
-#pragma unroll
-      for (int jj = 0; jj < JQ; ++jj)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          qv[jj][e] = macc[jj][8 * n + e];
-          va[jj][e] = 0.0f;
-        }
       auto row8 = [](const uint16_t* ring, size_t row, int c8) {
         return *reinterpret_cast<const uint4*>(ring + row * kD + 8 * c8);
       };
@@ -1191,38 +1188,56 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
           x[2 * e + 1] = __uint_as_float(u[e] & 0xffff0000u);
         }
       };
-      for (int c0 = 0; c0 < nr; c0 += 64) {
-        const int nc = min(64, nr - c0);
-        // positions 16 w + 4 i + gq of the chunk for the scores, 16 i + 4 w + gq for the values
-        uint4 kr[4], vr[4];
+      float va[KIVI ? JQ : 1][8];  // value sums over the passes
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          kr[i] = row8(a.kc.ring, ring0 + (r0 + c0 + min(16 * w + 4 * i + gq, nc - 1)) % ringsz, n);
+      for (int jj = 0; jj < (KIVI ? JQ : 1); ++jj)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) va[jj][e] = 0.0f;
+      // the four lane rows' sums of a query, then the four waves' (red is free: every wave has passed a barrier)
+      auto to_red = [&](int jj, const float (&v8)[8]) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          float v = v8[e];
+          v += __shfl_xor(v, 16);
+          v += __shfl_xor(v, 32);
+          if (gq == 0) red[(w * JQ + jj) * kD + 8 * n + e] = v;
+        }
+      };
+      for (int c0 = 0; c0 < (KIVI ? nr : 1); c0 += CH) {
+        const int nc = min(CH, nr - c0);
+        // positions 4 RI w + 4 i + gq of the pass for the scores, 16 i + 4 w + gq for the values
+        uint4 kr[RI], vr[RI];
+#pragma unroll
+        for (int i = 0; i < RI; ++i) {
+          kr[i] = row8(a.kc.ring, ring0 + (r0 + c0 + min(4 * RI * w + 4 * i + gq, nc - 1)) % ringsz, n);
           vr[i] = row8(a.vc.ring, ring0 + (r0 + c0 + min(16 * i + 4 * w + gq, nc - 1)) % ringsz, n);
         }
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < RI; ++i) {
           float x[8];
           lo_hi(kr[i], x);
-          const int r = 16 * w + 4 * i + gq;
+          const int r = 4 * RI * w + 4 * i + gq;
 #pragma unroll
           for (int jj = 0; jj < JQ; ++jj) {
+            const float4 q0 = *reinterpret_cast<const float4*>(&macc[jj][8 * n]);
+            const float4 q1 = *reinterpret_cast<const float4*>(&macc[jj][8 * n + 4]);
+            const float qv[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
             float z = 0.0f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) z = fmaf(qv[jj][e], x[e], z);
+            for (int e = 0; e < 8; ++e) z = fmaf(qv[e], x[e], z);
             z = row16_sum(z);
             if (n == jj) rs[jj][r] = jj < nj && r < nc ? a.scale * z : -INFINITY;
           }
         }
         __syncthreads();
         for (int jj = w; jj < JQ; jj += 4) {
-          const float sc = rs[jj][lane], mo = rml[0][jj];
+          const float sc = lane < CH ? rs[jj][lane % CH] : -INFINITY, mo = rml[0][jj];
           const float m = fmaxf(mo, wave_max(sc));
           const float p = sc == -INFINITY ? 0.0f : __expf(sc - m);
           const float f = mo == -INFINITY ? 0.0f : __expf(mo - m);
           const float sum = wave_sum(p);
-          rs[jj][lane] = p;
+          if (lane < CH) rs[jj][lane % CH] = p;
           if (lane == 0) {
             rml[0][jj] = m;
             rml[1][jj] = fmaf(rml[1][jj], f, sum);
@@ -1230,37 +1245,40 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
           }
         }
         __syncthreads();
+        if constexpr (KIVI) {
 #pragma unroll
-        for (int jj = 0; jj < JQ; ++jj) {
-          const float f = rfac[jj];
+          for (int jj = 0; jj < JQ; ++jj) {
+            const float f = rfac[jj];
 #pragma unroll
-          for (int e = 0; e < 8; ++e) va[jj][e] *= f;
+            for (int e = 0; e < 8; ++e) va[jj][e] *= f;
+          }
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < RI; ++i) {
           const int r = 16 * i + 4 * w + gq;
-          // rows past the chunk repeat its last one with weight 0: zeros, since 0 times an infinity is not 0
+          // rows past the pass repeat its last one with weight 0: zeros, since 0 times an infinity is not 0
           const uint32_t live = r < nc ? 0xffffffffu : 0u;
           float x[8];
           lo_hi(make_uint4(vr[i].x & live, vr[i].y & live, vr[i].z & live, vr[i].w & live), x);
 #pragma unroll
           for (int jj = 0; jj < JQ; ++jj) {
             const float p = rs[jj][r];
+            if constexpr (KIVI) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) va[jj][e] = fmaf(p, x[e], va[jj][e]);
+              for (int e = 0; e < 8; ++e) va[jj][e] = fmaf(p, x[e], va[jj][e]);
+            } else {
+              float v8[8];
+#pragma unroll
+              for (int e = 0; e < 8; ++e) v8[e] = p * x[e];
+              to_red(jj, v8);
+            }
           }
         }
       }
-      // the four lane rows' sums, then the four waves' (red is free: every wave has passed the barriers)
+      if constexpr (KIVI) {
 #pragma unroll
-      for (int jj = 0; jj < JQ; ++jj)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          float v = va[jj][e];
-          v += __shfl_xor(v, 16);
-          v += __shfl_xor(v, 32);
-          if (gq == 0) red[(w * JQ + jj) * kD + 8 * n + e] = v;
-        }
+        for (int jj = 0; jj < JQ; ++jj) to_red(jj, va[jj]);
+      }
       __syncthreads();
       for (int idx = threadIdx.x; idx < JQ * kD; idx += kAThreads)
         (&accr[0][0])[idx] = (red[idx] + red[JQ * kD + idx]) + (red[2 * JQ * kD + idx] + red[3 * JQ * kD + idx]);
@@ -1345,7 +1363,11 @@ __global__ __launch_bounds__(kAThreads, 2) void att_mfma(AttendDev a, GaugeDev G
     __syncthreads();
   }
   if (a.nsplit == 1) {
-    finalize_rows<JQ>(a, G, out, &macc[0][0], RAW ? &accr[0][0] : nullptr, mm[1], nj, lv, b, h, hq0, red);
+    for (int jj = 0; jj < nj; jj += FJ) {
+      if (jj) __syncthreads();  // the sums of the queries before are read
+      finalize_rows<FJ>(a, G, out, &macc[jj][0], RAW ? &accr[RAW ? jj : 0][0] : nullptr, mm[1] + jj, min(FJ, nj - jj), lv, b,
+                        h, hq0 + jj, red);
+    }
     return;
   }
   const size_t pstride = size_t(2 + 2 * kD);
