@@ -750,7 +750,7 @@ __device__ __forceinline__ void gauge_query(const QueryRows& q, const GaugeDev& 
 }
 
 template <int BITS, int NBLK, int TB, bool KIVI = false>
-__global__ __launch_bounds__(kAThreads, 3) void att_mfma(AttendDev a, GaugeDev G) {
+__global__ __launch_bounds__(kAThreads, KIVI ? 3 : 2) void att_mfma(AttendDev a, GaugeDev G) {
   static_assert(TB == 1 || TB == 16, "token tiles of 16");
   static_assert(!KIVI || (TB == 1 && NBLK == 2), "KIVI: 32-position key groups, 64-channel value blocks");
   constexpr bool RAW = TB > 1 || KIVI;         // raw bf16 positions after the quantised ones
@@ -1164,9 +1164,9 @@ __global__ __launch_bounds__(kAThreads, 3) void att_mfma(AttendDev a, GaugeDev G
   // maximum moves.  One workgroup per row has them all, so their latency adds to the launch: with
   // one thread per position reading its row 2 bytes at a time, the 128 to 159 positions of a KIVI window
   // were 146 of a 380 us launch (8 layers x 4 rows x 8 heads x 16000 positions, 3 bits).  Tiles take one pass of 16
-  // positions, and the query stays in LDS: with it and the sums of 64 positions held, every wave of the
-  // launch had 174 registers (KIVI, tiles with n = 64) or 246 (n = 128) and a SIMD two waves.  8 x 32 x 8 rows of
-  // 16384 positions: tiles, 4 bits, n = 64 897 -> 812 us, n = 128 990 -> 897; KIVI, 3 bits, 1397 -> 1185.
+  // positions and read the query from LDS, which leaves them the registers of three waves per SIMD or four;
+  // KIVI is held to three.  With two (174 registers; 246 for tiles with n = 128), 8 x 32 x 8 rows of 16384
+  // positions: tiles, 4 bits, n = 64 897 us against 790 now, n = 128 984 against 876; KIVI, 3 bits, 1398 against 1156.
   if constexpr (RAW) {
     constexpr int RI = KIVI ? 4 : 1, CH = 16 * RI;  // value rows per thread and pass, positions per pass
     const int ringsz = KIVI ? a.win + 32 : TB;
@@ -1188,6 +1188,17 @@ __global__ __launch_bounds__(kAThreads, 3) void att_mfma(AttendDev a, GaugeDev G
           x[2 * e + 1] = __uint_as_float(u[e] & 0xffff0000u);
         }
       };
+      auto query8 = [&](int jj, float (&q)[8]) {
+        const float4 q0 = *reinterpret_cast<const float4*>(&macc[jj][8 * n]);
+        const float4 q1 = *reinterpret_cast<const float4*>(&macc[jj][8 * n + 4]);
+        q[0] = q0.x; q[1] = q0.y; q[2] = q0.z; q[3] = q0.w;
+        q[4] = q1.x; q[5] = q1.y; q[6] = q1.z; q[7] = q1.w;
+      };
+      float qv[KIVI ? JQ : 1][8];
+      if constexpr (KIVI) {
+#pragma unroll
+        for (int jj = 0; jj < JQ; ++jj) query8(jj, qv[jj]);
+      }
       float va[KIVI ? JQ : 1][8];  // value sums over the passes
 #pragma unroll
       for (int jj = 0; jj < (KIVI ? JQ : 1); ++jj)
@@ -1195,12 +1206,18 @@ __global__ __launch_bounds__(kAThreads, 3) void att_mfma(AttendDev a, GaugeDev G
         for (int e = 0; e < 8; ++e) va[jj][e] = 0.0f;
       // the four lane rows' sums of a query, then the four waves' (red is free: every wave has passed a barrier)
       auto to_red = [&](int jj, const float (&v8)[8]) {
+        float v[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          float v = v8[e];
-          v += __shfl_xor(v, 16);
-          v += __shfl_xor(v, 32);
-          if (gq == 0) red[(w * JQ + jj) * kD + 8 * n + e] = v;
+          const auto u = __builtin_amdgcn_permlane16_swap(__float_as_uint(v8[e]), __float_as_uint(v8[e]), false, false);
+          const uint32_t h = __float_as_uint(__uint_as_float(u[0]) + __uint_as_float(u[1]));
+          const auto t = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+          v[e] = __uint_as_float(t[0]) + __uint_as_float(t[1]);
+        }
+        if (gq == 0) {
+          float4* dst = reinterpret_cast<float4*>(red + (w * JQ + jj) * kD + 8 * n);
+          dst[0] = make_float4(v[0], v[1], v[2], v[3]);
+          dst[1] = make_float4(v[4], v[5], v[6], v[7]);
         }
       };
       for (int c0 = 0; c0 < (KIVI ? nr : 1); c0 += CH) {
@@ -1220,12 +1237,11 @@ __global__ __launch_bounds__(kAThreads, 3) void att_mfma(AttendDev a, GaugeDev G
           const int r = 4 * RI * w + 4 * i + gq;
 #pragma unroll
           for (int jj = 0; jj < JQ; ++jj) {
-            const float4 q0 = *reinterpret_cast<const float4*>(&macc[jj][8 * n]);
-            const float4 q1 = *reinterpret_cast<const float4*>(&macc[jj][8 * n + 4]);
-            const float qv[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
+            if constexpr (!KIVI) query8(jj, qv[0]);
+            const float (&q)[8] = qv[KIVI ? jj : 0];
             float z = 0.0f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) z = fmaf(qv[e], x[e], z);
+            for (int e = 0; e < 8; ++e) z = fmaf(q[e], x[e], z);
             z = row16_sum(z);
             if (n == jj) rs[jj][r] = jj < nj && r < nc ? a.scale * z : -INFINITY;
           }
@@ -1255,18 +1271,24 @@ __global__ __launch_bounds__(kAThreads, 3) void att_mfma(AttendDev a, GaugeDev G
         }
 #pragma unroll
         for (int i = 0; i < RI; ++i) {
+          // rows past the pass repeat its last one with weight 0 and are left out: 0 times an infinity is not 0
           const int r = 16 * i + 4 * w + gq;
-          // rows past the pass repeat its last one with weight 0: zeros, since 0 times an infinity is not 0
-          const uint32_t live = r < nc ? 0xffffffffu : 0u;
           float x[8];
-          lo_hi(make_uint4(vr[i].x & live, vr[i].y & live, vr[i].z & live, vr[i].w & live), x);
+          if constexpr (KIVI) {
+            if (r < nc) {
+              lo_hi(vr[i], x);
 #pragma unroll
-          for (int jj = 0; jj < JQ; ++jj) {
-            const float p = rs[jj][r];
-            if constexpr (KIVI) {
+              for (int jj = 0; jj < JQ; ++jj) {
+                const float p = rs[jj][r];
 #pragma unroll
-              for (int e = 0; e < 8; ++e) va[jj][e] = fmaf(p, x[e], va[jj][e]);
-            } else {
+                for (int e = 0; e < 8; ++e) va[jj][e] = fmaf(p, x[e], va[jj][e]);
+              }
+            }
+          } else {
+            lo_hi(r < nc ? vr[i] : make_uint4(0u, 0u, 0u, 0u), x);
+#pragma unroll
+            for (int jj = 0; jj < JQ; ++jj) {
+              const float p = rs[jj][r];
               float v8[8];
 #pragma unroll
               for (int e = 0; e < 8; ++e) v8[e] = p * x[e];
