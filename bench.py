@@ -53,8 +53,8 @@ def algorithmic_bytes(w, s_count=1):
 
 
 def kernel_source_hash():
-    """First 16 hex digits of the SHA-256 of the matrix-core kernel sources (cg_mfma.hip followed by
-    its shared header cg_mfma_util.h)."""
+    """First 16 hex digits of the SHA-256 of the matrix-core kernel sources: the decoders, the encoder and
+    the two headers they share, in this order."""
     import hashlib
 
     h = hashlib.sha256()

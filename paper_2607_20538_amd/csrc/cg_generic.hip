@@ -579,20 +579,23 @@ __global__ __launch_bounds__(kThreads, general_waves(KR, NBW, STORE)) void dec_g
 
 // KIVI tiles are exactly one key token group, so the quantised / window split (a multiple of
 // the group) never cuts a tile.  Otherwise a tile holds about 4096 values, two granules of 8 channels per
-// thread: 64 tokens for heads of at most 64 channels (where that leaves every CU a workgroup of at least
-// two tiles), 32 up to 128 channels, 16 above.  Paged caches take at most 32: positions start at
-// multiples of 32, so only such a tile always lies inside one page; block-uniform tiles take whole ones.
+// thread: 64 tokens for heads of at most 64 channels where that leaves every CU a workgroup of at least
+// two tiles, 32 up to 128 channels, 16 above.  (32 against 64 tokens, encode / decode of a bf16 tensor,
+// d = 64: 2^15 tokens 7.4 / 8.9 against 6.3 / 8.3 us, 2^19 46 / 62 against 41 / 60; d = 32: 2^15 7.3 / 7.2 against
+// 7.1 / 7.3, 2^19 37 / 35 against 26 / 28; below 2^15 the two are within 1 us either way.)  Paged caches take at
+// most 32: positions start at multiples of 32, so only such a tile always lies inside one page;
+// block-uniform tiles take whole ones.
 int tile_tokens(const CodecDev& c, int d, bool paged, int T, int nslices) {
   if (c.backend == CG_BACKEND_KIVI) return c.kg;
   if (d > 128) return c.backend == CG_BACKEND_BLOCK_UNIFORM && c.bt > 16 ? 32 : 16;
-  return !paged && d <= 64 && int64_t(T) * nslices >= 64 * 512 ? 64 : 32;
+  return !paged && d <= 64 && int64_t(T) * nslices >= 64 * 2 * cu_count() ? 64 : 32;
 }
 
-// Tiles per workgroup: each slice in as many chunks as bring the workgroups to about 1024 (four per
-// CU, all resident), so that a gauge is loaded once per several tiles and the next tile's loads run
+// Tiles per workgroup: each slice in as many chunks as bring the workgroups to about four per CU, all
+// resident, so that a gauge is loaded once per several tiles and the next tile's loads run
 // beside this one's work; one tile while there are fewer than that.
 int tiles_per_wg(int ntiles, int nslices) {
-  const int chunks = std::max(1, std::min(ntiles, (1024 + nslices / 2) / nslices));
+  const int chunks = std::max(1, std::min(ntiles, (4 * cu_count() + nslices / 2) / nslices));
   return (ntiles + chunks - 1) / chunks;
 }
 

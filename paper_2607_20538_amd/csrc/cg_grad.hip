@@ -1087,13 +1087,13 @@ hipError_t launch_gauge_grad(int s, const ViewDev& X, const GaugeDev& G, const f
   a.chunks = lay.chunks;
   a.blocks_per_wg = lay.blocks_per_wg;
   if (groups) {
-    // Two workgroups a CU are resident, 512 on the chip, and each sets up its fragments for about two
-    // blocks' time: the split (never more chunks than the workspace holds) whose waves of workgroups end first.
+    // Two workgroups a CU are resident, and each sets up its fragments for about two blocks' time: the split (never more chunks than the workspace holds) whose waves of workgroups end first.
     const int64_t sl = int64_t(X.L) * X.B * X.H;
+    const int slots = 2 * cu_count();
     int64_t best = 0;
     for (int ch = 1; ch <= lay.chunks; ++ch) {
       const int bpw = (nblk + ch - 1) / ch;
-      const int64_t cost = (sl * ch + 511) / 512 * (bpw + 2);
+      const int64_t cost = (sl * ch + slots - 1) / slots * (bpw + 2);
       if (ch == 1 || cost < best) {
         best = cost;
         a.blocks_per_wg = std::max(bpw, 1);

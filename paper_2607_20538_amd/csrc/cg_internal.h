@@ -13,6 +13,17 @@ namespace cg {
 // Split planes of G^T the matrix-core decoders multiply (G^T ~= tr[0] + tr[1]).
 constexpr int kDecPlanes = 2;
 
+// Compute units of the device that is current at the first call (256 on an MI355X)
+inline int cu_count() {
+  static const int cus = [] {
+    int dev = 0, n = 0;
+    const bool ok = hipGetDevice(&dev) == hipSuccess &&
+                    hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0;
+    return ok ? n : 256;
+  }();
+  return cus;
+}
+
 // Device gauge buffer (filled by gauge_make):
 //   f32  : G            [nblk][g][g] binary32, nblk = L*2*H*R, block ((l*2+s)*H+h)*R+r
 //   hi[p]: split planes of G,   bf16 [nblk][g][g], G ~= hi[0] + hi[1] + hi[2]

@@ -73,16 +73,6 @@ __device__ void load_a(bf16x8_t (&A)[NP][KS], const MfmaArgs& a, int l, int h, i
   }
 }
 
-inline int cu_count() {
-  static int cus = 0;
-  if (!cus) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-      cus = 256;
-  }
-  return cus;
-}
-
 // Split the (slice, tile) space into workgroups: as many as can be resident at once (the
 // kernel's occupancy per CU times the CUs), each a contiguous tile range of one slice; the
 // count is padded to a multiple of 8 (XCD remap).
