@@ -8,8 +8,7 @@
 // from global memory into the operand registers), so a gauge is read once per 16 rows and all of
 // its loads are in flight together.  Measured on MI355X, K and V of one layer of 8 heads, d = g = 128,
 // batch 1: 41 us in two launches (a 128-step chain of dependent 4-byte-per-lane loads and a block
-// quantised by one thread) -> 7 us in one (kernel time by its phases: 1 us to the first loads, 2 us
-// loads, 1.3 us gauge, 1.2 us quantiser).
+// quantised by one thread) -> 7 us in one.
 #include "cg_internal.h"
 #include "cg_device.h"
 #include "cg_general.h"
